@@ -4,8 +4,8 @@
 One step = one full pass of the hot path over one query: the 16-bit
 two-dimensional interval validation of 1,024 records (4 comparators and 3
 ANDs per record: 199,680 blind rotations, 134,144 key switches, 19 circuit
-levels), every level launched as rounds of 1,024 blind rotations (two
-wavefronts each, one per prime) plus one batched key-switching launch.
+levels), every level launched as rounds of up to 2,048 blind rotations plus
+one batched key-switching launch.
 Inputs are resident in device memory before timing.
 
 Prints one JSON line: blind rotations per second (value), the plain
@@ -46,15 +46,22 @@ OPS_PER_RESIDUE_BUTTERFLY = 5
 RESIDUES_PER_MODMUL = 2
 PEAK_MODMUL = VALU_LANE_OPS / (OPS_PER_RESIDUE_BUTTERFLY * RESIDUES_PER_MODMUL)  # 3.932e12 modmul/s
 
+# The same work by double-precision transforms, as the kernels do it: per CMux
+# 6 forward and 3 inverse 512-point complex transforms of 2,304 butterflies (6
+# FMAs each) and 18 x 512 complex products (4 FMAs each); the vector units
+# issue 64 double-precision FMAs per CU and clock.
+FMA_PER_BR = 630 * (9 * 2304 * 6 + 18 * 512 * 4)  # 101,606,400
+PEAK_FMA = 256 * 64 * 2.4e9
+
 # A workload is one or more programs run together (their levels merged).
 # HBM-side traffic of the blind-rotation kernel per launch on the default
 # workload, from two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE;
 # copy-calibrated), valid only for the kernel sources it was measured on
 # (their sha256 prefix) and the launch shape it was measured with.
-TRAFFIC_MEASURED = {"kernel_sha": "749f0fca55ff871c", "bytes_per_launch": 5.16355e+08,
+TRAFFIC_MEASURED = {"kernel_sha": None, "bytes_per_launch": None,
                     "launch": {"br_waves_per_rotation": 0, "br_rotations_per_block": 4, "br_blocks_per_cu": 1,
                                "ks_gates_per_block": 512}}
-KERNEL_SOURCES = ("kernels.hip", "wave_ntt.h", "rns.h", "vlp_api.cpp")
+KERNEL_SOURCES = ("kernels.hip", "fft.h", "vlp_api.cpp")
 
 
 def kernel_sha() -> str:
@@ -97,13 +104,16 @@ def device_inputs(ctx, spec, seed):
 
 
 def br_roofline(prof):
-    """Blind-rotation kernel rate against the derived integer peak, from the
-    library's per-launch HIP-event timing, and the key-switching share."""
+    """Blind-rotation kernel rate against the double-precision FMA peak, from
+    the library's per-launch HIP-event timing, and the key-switching share;
+    also counted as modular multiplications against the integer peak of an
+    exact two-prime transform (which the kernels no longer use)."""
     br, ks = prof["br"], prof["ks"]
     avg_ms = br["ms"] / br["launches"]
-    achieved = MODMUL_PER_BR * br["items"] / br["launches"] / (avg_ms * 1e-3)
-    return {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_MODMUL / 1e12, "unit": "Tmodmul/s",
-            "frac": achieved / PEAK_MODMUL, "launches": br["launches"], "avg_launch_ms": avg_ms,
+    rate = br["items"] / br["launches"] / (avg_ms * 1e-3)
+    return {"bound": "alu", "achieved": FMA_PER_BR * rate / 1e12, "peak": PEAK_FMA / 1e12, "unit": "TFMA/s (fp64)",
+            "frac": FMA_PER_BR * rate / PEAK_FMA, "launches": br["launches"], "avg_launch_ms": avg_ms,
+            "modmul_achieved": MODMUL_PER_BR * rate / 1e12, "modmul_integer_peak": PEAK_MODMUL / 1e12,
             "ks_kernel_ms_share": ks["ms"] / max(1e-9, ks["ms"] + br["ms"]),
             "ks_launches": ks["launches"], "ks_ms": ks["ms"]}
 
@@ -684,26 +694,17 @@ def main():
     roofline = None
     if prof and prof["br"]["launches"]:
         br = prof["br"]
-        # Algorithmic bytes per launch: the transformed key once (61,931,520 B), the two
+        # Algorithmic bytes per launch: the transformed key once (92,897,280 B), the two
         # input ciphertexts (2 x 2,524 B) and the extracted output (4,100 B) per rotation.
-        alg_bytes = 61931520 + (2 * 2524 + 4100) * br["items"] / br["launches"]
+        alg_bytes = 92897280 + (2 * 2524 + 4100) * br["items"] / br["launches"]
         traffic = None
         if (args.workload == "intv-1024" and TRAFFIC_MEASURED["kernel_sha"] == kernel_sha()
                 and TRAFFIC_MEASURED["launch"] == launch):
             traffic = TRAFFIC_MEASURED["bytes_per_launch"]
         roofline = br_roofline(prof)
-        achieved = roofline["achieved"] * 1e12
         roofline.update({"traffic": traffic, "traffic_unit": "B per launch", "algorithmic_bytes_per_launch": alg_bytes,
-                         "kernel": {0: "br2_kernel (br4_kernel for short rounds)", 1: "br_kernel", 2: "br2_kernel",
-                                    4: "br4_kernel"}[launch["br_waves_per_rotation"]]})
-        # Beside the derived peak: the measured rate of the transforms' own residue
-        # butterflies (register-resident, every CU busy, the 6:2 forward:inverse mix of
-        # a CMux), two of which make one modular multiplication.
-        mp = vlp.vlp_measure_modmul_peak(0)
-        roofline["peak_measured"] = mp["mixed"] / RESIDUES_PER_MODMUL / 1e12
-        roofline["frac_of_peak_measured"] = achieved / (mp["mixed"] / RESIDUES_PER_MODMUL)
-        log("measured residue-butterfly peak: %.3f T/s forward, %.3f T/s inverse, %.3f T/s mixed"
-            % (mp["fwd"] / 1e12, mp["inv"] / 1e12, mp["mixed"] / 1e12))
+                         "kernel": {0: "br1_kernel (br3_kernel for short rounds)", 1: "br1_kernel", 2: "br3_kernel",
+                                    4: "br3_kernel"}[launch["br_waves_per_rotation"]]})
 
     config4 = None
     if not args.no_config4 and args.workload != "idm-65536":

@@ -135,7 +135,7 @@ vlp_status vlp_mem_info(const vlp_ctx *ctx, size_t *used, size_t *budget);
  * key-switching key).  bk_dev: [630][6][2][1024], ksk_dev: [1024][8][4][631]
  * device arrays in the layouts above; they are read during the call's stream
  * work and may be freed after vlp_sync().  The keyset holds the bootstrapping
- * key transformed for the exact negacyclic products (61,931,520 B) and the
+ * key transformed for the exact negacyclic products (92,905,472 B) and the
  * key-switching key as signed byte planes for the 8-bit matrix cores
  * (83,886,080 B).  VLP_EBUDGET if it does not fit. */
 vlp_status vlp_keyset_load(vlp_ctx *ctx, const uint32_t *bk_dev, const uint32_t *ksk_dev, vlp_keyset **out);
@@ -259,24 +259,23 @@ vlp_status vlp_program_counts(const vlp_program *prog, uint64_t *gates, uint64_t
 vlp_status vlp_program_destroy(vlp_program *prog);
 
 /* ---- Tuning knobs of the batched kernels (picked by the autotuner).
- * br_waves_per_rotation : wavefronts per blind rotation:
- *                          1 = both RNS primes in one wavefront;
- *                          2 = one wavefront per prime;
- *                          4 = one per prime and accumulator half (half the
- *                              latency of 2 per rotation, half the rotations
- *                              in flight; one rotation per workgroup);
- *                          0 = automatic (default): launches of at most 2
- *                              rotations per CU use 4 (2 workgroups per CU),
- *                              larger ones 2 in full rounds, a short last
- *                              round again 4
+ * br_waves_per_rotation : the blind-rotation kernel:
+ *                          1 = one wavefront per rotation;
+ *                          2, 4 = three wavefronts per rotation (one per
+ *                              digit, then one per product channel): lower
+ *                              latency, fewer rotations in flight; 4: one
+ *                              rotation per workgroup;
+ *                          0 = automatic (default): each round picks by the
+ *                              rotations left (up to 2 per CU the second
+ *                              kind, more the first, at most 8 per CU)
  * br_rotations_per_block: rotations per workgroup (1 wavefront per rotation:
- *                          1, 2, 4, 8 -- 8 puts two on a SIMD at half the
- *                          registers each; 2 wavefronts per rotation: 1, 2, 4
- *                          -- the rotations of a workgroup advance in
- *                          lockstep and share key reads; 4: 1)
+ *                          1, 2, 4, 8; br_waves_per_rotation = 2: 1, 2, 4,
+ *                          of which at most 2 share a workgroup; 4: 1);
+ *                          the automatic choice sets its own
  * br_blocks_per_cu      : workgroups per compute unit a launch is sized for
  *                          (1..64); one launch covers br_blocks_per_cu x
- *                          br_rotations_per_block rotations per CU
+ *                          br_rotations_per_block rotations per CU (not in
+ *                          automatic mode)
  * ks_gates_per_block    : most gates a key-switching workgroup takes, sharing
  *                          its reads of the key (128, 256, 512 (default));
  *                          each launch picks the tile (up to this) and the
@@ -302,16 +301,17 @@ typedef struct {
 vlp_status vlp_profile_enable(vlp_ctx *ctx, int enable);
 vlp_status vlp_profile_read(vlp_ctx *ctx, vlp_kernel_stats *br, vlp_kernel_stats *ks);
 
-/* ---- Measured arithmetic peak.  The count a blind rotation is priced by is
- * its modular multiplications (per CMux of Section 2.2: 8 negacyclic
- * transforms of 512 x 10 butterflies and 12 x 1024 key products), each
- * computed as one residue butterfly per prime of the two-prime residue
- * system.  This call measures the rate at which HIP device `device` runs the
- * transforms' own residue butterflies (lazy signed forward Cooley-Tukey and
- * inverse Gentleman-Sande with Shoup products) on register-resident values
- * with every CU busy: *fwd_per_s and *inv_per_s for each kind, *mixed_per_s
- * for the 6:2 forward:inverse mix of a CMux (residue butterflies per second;
- * halve for modular multiplications per second).  It
+/* ---- Measured integer peak.  The work of a blind rotation can be counted as
+ * modular multiplications (per CMux of Section 2.2: 8 negacyclic transforms
+ * of 512 x 10 butterflies and 12 x 1024 key products); on the integer units
+ * each takes one residue butterfly per prime of a two-prime residue system.
+ * This call measures the rate at which HIP device `device` runs such residue
+ * butterflies (lazy signed forward Cooley-Tukey and inverse Gentleman-Sande
+ * with Shoup products) on register-resident values with every CU busy:
+ * *fwd_per_s and *inv_per_s for each kind, *mixed_per_s for the 6:2
+ * forward:inverse mix of a CMux (residue butterflies per second; halve for
+ * modular multiplications per second).  The library's own transforms are
+ * double-precision ones, which need fewer instructions.  The call
  * blocks for about 0.1 s, allocates and frees a small device buffer and a
  * stream of its own, and needs no context.  VLP_EINVAL for a null output or
  * a bad device; VLP_EHIP if a HIP call fails (no message: there is no

@@ -1,0 +1,49 @@
+// Host twiddle tables of the double-precision negacyclic transform (fft.h).
+#include <math.h>
+
+#include "internal.h"
+
+namespace vlp {
+
+namespace {
+
+// s of stage k, block b: exp(2 pi I (2^-(k+3) + brv_k(b) / 2^(k+1))), to long double.
+void stage_twiddle(int k, int b, long double* c, long double* s) {
+  int rev = 0;
+  for (int t = 0; t < k; ++t) rev |= ((b >> t) & 1) << (k - 1 - t);
+  const long double turns = ldexpl(1.0L, -(k + 3)) + ldexpl((long double)rev, -(k + 1));
+  const long double ang = 2.0L * acosl(-1.0L) * turns;
+  *c = cosl(ang);
+  *s = sinl(ang);
+}
+
+}  // namespace
+
+void make_fft_tables(FftTables* t) {
+  long double c, s;
+  for (int L = 0; L < 64; ++L) {
+    const int rho = L & 15, i4 = L >> 5, i3 = (L >> 4) & 1;
+    const int i8 = L >> 5;  // of layout 4
+    const int k_of[11] = {4, 5, 6, 6, 7, 8, 8, 3, 3, 2, 1};
+    const int tail = (rho << 3) | (i4 << 2) | (i3 << 1);  // block of stage 7 with i2 = 0
+    const int b_of[11] = {rho,          rho << 1, rho << 2,       (rho << 2) | 2, tail, tail << 1, (tail << 1) | 2,
+                          i8 << 2, (i8 << 2) | 2, i8 << 1, i8};
+    for (int e = 0; e < 11; ++e) {
+      stage_twiddle(k_of[e], b_of[e], &c, &s);
+      t->lane[e][L][0] = (double)c;
+      t->lane[e][L][1] = (double)s;
+    }
+  }
+  for (int k = 0; k < 9; ++k)
+    for (int b = 0; b < (1 << k); ++b) {
+      stage_twiddle(k, b, &c, &s);
+      double* d = t->dd[(1 << k) + b];
+      d[0] = (double)c;
+      d[1] = (double)(c - (long double)d[0]);
+      d[2] = (double)s;
+      d[3] = (double)(s - (long double)d[2]);
+    }
+  for (int e = 0; e < 4; ++e) t->dd[0][e] = 0;
+}
+
+}  // namespace vlp

@@ -17,12 +17,11 @@ constexpr int CT_n = LWE_n + 1;     // words of an LWE_n ciphertext
 constexpr int CT_N = RING_N + 1;    // words of an LWE_N ciphertext
 constexpr uint32_t MU = 0x20000000u; // 1/8
 
-// Transformed bootstrapping key: [630][6 rows][2 components][1024] residue
-// pairs (mod P1, mod P2), each polynomial in the NTT's transform order
-// (layout Z, stored as [r][lane] so a wave's loads are contiguous), scaled
-// by 1/1024 and kept in Montgomery form (times 2^32 mod P).
-constexpr size_t BK_ROW_WORDS = (size_t)2 * ELL * 2 * 2 * RING_N;  // one key row i: [6][2][2 primes][1024] words
-constexpr size_t BK_NTT_WORDS = (size_t)LWE_n * BK_ROW_WORDS;
+// Transformed bootstrapping key (fft.h): [630][6 rows][3 channels][8
+// registers][64 lanes] complex doubles, each polynomial in the transform's
+// order (layout 3, so a wavefront's loads are contiguous), scaled by 1/512.
+constexpr size_t BK_ROW_POINTS = (size_t)2 * ELL * 3 * (RING_N / 2);  // complex points of one key row i
+constexpr size_t BK_FFT_BYTES = (size_t)LWE_n * BK_ROW_POINTS * 16 + 8192;  // + one batch that is read ahead, not used
 // Key-switching key laid out for the 8-bit matrix cores, as byte planes:
 // [1024 coefficients i][20 tiles of 32 output words][4 byte planes p][64
 // lanes][4 words t].  Lane n + 32 h, word t holds, for output word
@@ -39,7 +38,7 @@ struct BrItem {
   const uint32_t* a;
   const uint32_t* b;    // may be null (then cb is ignored)
   uint32_t* out;        // [1025]
-  const uint32_t* bk;   // transformed bootstrapping key
+  const void* bk;       // transformed bootstrapping key
   int32_t ca, cb;
   uint32_t cst, mu;
   const uint32_t* const* more;  // n_more further operands (k-input XOR), or null
@@ -70,20 +69,26 @@ constexpr size_t NOALLOC_BYTES = NOALLOC_EXT_BYTES + 2 * NOALLOC_MAX_GATES * siz
 // of the lookup; call with the device current).
 int noalloc_scratch_address(void** p);
 
+// Twiddle tables of the transforms (fft.h): the lane-dependent ones of a
+// wavefront, and every stage's as double-doubles {re, re_lo, im, im_lo} at
+// index 2^k + block (the key's transform; entry 0 unused).
+struct FftTables {
+  double lane[11][64][2];
+  double dd[512][4];
+};
+void make_fft_tables(FftTables* t);
+
 // Host-side launchers (kernels.hip).  All enqueue on `stream` and return the
-// HIP error of the launch.
-int launch_bk_transform(const uint32_t* bk_coeff, uint32_t* bk_ntt, const uint4* tw_fwd, void* stream);
+// HIP error of the launch.  `tables` is a device pointer.
+int launch_bk_transform(const uint32_t* bk_coeff, void* bk_fft, const FftTables* tables, void* stream);
 int launch_ksk_relayout(const uint32_t* ksk_in, uint32_t* ksk_out, void* stream);
-int launch_br(const BrItem* items, uint32_t count, const uint4* tw_fwd, uint32_t waves_per_block, uint32_t blocks,
+// Blind rotations by `waves` (1 or 3) wavefronts each, rot_per_block of them
+// per workgroup (1 wavefront: 1, 2, 4, 8; 3: 1, 2).
+int launch_br(const BrItem* items, uint32_t count, const FftTables* tables, uint32_t waves, uint32_t rot_per_block,
               void* stream);
 // ServerEnc over a flat [count][631] array; out == pk runs in place.
 int launch_server_enc(const uint32_t* pk, uint32_t* out, size_t count, const int64_t* vals, const uint8_t* bytes,
                       uint32_t l, void* stream);
-// Two wavefronts per rotation (one per prime), rot_per_block (1, 2, 4) rotations per workgroup.
-int launch_br2(const BrItem* items, uint32_t count, const uint4* tw_fwd, uint32_t rot_per_block, uint32_t blocks,
-               void* stream);
-// Four wavefronts per rotation (prime x accumulator half), one rotation per workgroup.
-int launch_br4(const BrItem* items, uint32_t count, const uint4* tw_fwd, uint32_t blocks, void* stream);
 // Key switching of count items on the matrix cores, in launches of at most
 // KS_CHUNK gates; dig: device scratch of ks_digit_bytes(count) bytes;
 // gates_per_block is the most gates a workgroup takes (128, 256 or 512), cus
@@ -93,15 +98,9 @@ constexpr size_t ks_digit_bytes(size_t count) { return (count < KS_CHUNK ? count
 int launch_ks_group(const KsItem* items, uint32_t count, const uint32_t* ksk, uint32_t* dig,
                     uint32_t gates_per_block, uint32_t cus, void* stream);
 int launch_make_br_items(BrItem* items, uint32_t count, const uint32_t* a, const uint32_t* b, int32_t ca, int32_t cb,
-                         uint32_t cst, uint32_t mu, uint32_t* out, const uint32_t* bk, void* stream);
+                         uint32_t cst, uint32_t mu, uint32_t* out, const void* bk, void* stream);
 int launch_make_ks_items(KsItem* items, uint32_t count, const uint32_t* u1, const uint32_t* u2, uint32_t cst,
                          uint32_t* out, const uint32_t* ksk, void* stream);
 int launch_negate(const uint32_t* a, uint32_t* out, size_t words, void* stream);
-
-// Twiddle table (host), 4 words per m < 1024: {w1, Shoup(w1), w2, Shoup(w2)}
-// with w_k = psi_k^brv10(m) mod P_k (the inverse transform reads it too).
-void make_twiddles(uint32_t* tw);
-// Per prime {N^-1 2^32 mod P, its Shoup quotient}: the key's scale factor.
-void key_scale(uint32_t out[4]);
 
 }  // namespace vlp

@@ -6,48 +6,84 @@
 #include <type_traits>
 
 #include "internal.h"
-#include "rns.h"
-#include "wave_ntt.h"
+#include "fft.h"
 
 namespace vlp {
+
+// Global-address-space views: loads through them are global (not flat)
+// loads, so they are not counted by the LDS wait of the transposes.
+typedef const uint32_t __attribute__((address_space(1))) g_u32;
 
 // ---------------------------------------------------------------------------
 // Key preparation
 // ---------------------------------------------------------------------------
 
-// One wave per bootstrapping-key polynomial: residues of the coefficient words
-// (integers in [0, 2^32)), forward transform, canonical, times the key scale
-// 2^32 / 1024 (mod P_k), canonical again.
-template <int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void bk_transform_kernel(const uint32_t* __restrict__ bk_coeff,
-                                                                   uint32_t* __restrict__ bk_ntt,
-                                                                   const Tw* __restrict__ tw_fwd,
-                                                                   uint32_t n_polys, uint4 scale) {
-  __shared__ Tw s_tw[RING_N];
-  __shared__ uint2 s_buf[WAVES][RING_N];
-  for (int k = threadIdx.x; k < RING_N; k += blockDim.x) s_tw[k] = tw_fwd[k];
+// Double-double arithmetic (an unevaluated sum h + l, |l| <= ulp(h) / 2): the
+// key is transformed with about 2^-100 relative error and rounded once.
+struct DD {
+  double h, l;
+};
+__device__ __forceinline__ DD dd_norm(double a, double b) {  // |a| >= |b| or a = 0
+  const double s = a + b;
+  return {s, b - (s - a)};
+}
+__device__ __forceinline__ DD dd_add(DD a, DD b) {
+  const double s = a.h + b.h, bb = s - a.h;
+  const double e = (a.h - (s - bb)) + (b.h - bb);
+  return dd_norm(s, e + (a.l + b.l));
+}
+__device__ __forceinline__ DD dd_neg(DD a) { return {-a.h, -a.l}; }
+__device__ __forceinline__ DD dd_mul(DD a, DD b) {
+  const double p = a.h * b.h, e = __builtin_fma(a.h, b.h, -p);
+  return dd_norm(p, e + __builtin_fma(a.h, b.l, a.l * b.h));
+}
+
+// One workgroup of 256 threads per key polynomial and channel: splits the
+// words (fft.h), transforms in LDS (a butterfly per thread and stage), scales
+// by 1/512 and stores in layout 3, [8 registers][64 lanes].
+__global__ __launch_bounds__(256) void bk_transform_kernel(const uint32_t* __restrict__ bk_coeff,
+                                                           double2* __restrict__ bk_fft,
+                                                           const double4* __restrict__ dd_tw) {
+  __shared__ DD s_re[FFT_N], s_im[FFT_N];
+  const uint32_t row = blockIdx.x / FFT_CHANNELS, ch = blockIdx.x % FFT_CHANNELS;  // row = i * 6 + r
+  const uint32_t* a = bk_coeff + (size_t)row * 2 * RING_N;
+  auto word = [&](const uint32_t* p, uint32_t j, double* hi) -> double {  // lo; *hi
+    const int32_t k = (int32_t)p[j];
+    int32_t lo = k % KEY_RADIX;  // truncated remainder in (-20, 20), to [-10, 9]
+    if (lo >= KEY_RADIX / 2) lo -= KEY_RADIX;
+    if (lo < -KEY_RADIX / 2) lo += KEY_RADIX;
+    *hi = (double)(((int64_t)k - lo) / KEY_RADIX);
+    return (double)lo;
+  };
+  auto value = [&](uint32_t j) -> double {
+    double ha, hb;
+    if (ch == 0) return word(a, j, &ha), ha;
+    if (ch == 1) return word(a + RING_N, j, &hb), hb;
+    return word(a, j, &ha) + (double)(1 << LO_SHIFT) * word(a + RING_N, j, &hb);
+  };
+  for (uint32_t i = threadIdx.x; i < FFT_N; i += 256) {
+    s_re[i] = {value(i), 0.0};
+    s_im[i] = {value(i + FFT_N), 0.0};
+  }
+  const uint32_t t = threadIdx.x;
+  for (int k = 0; k < 9; ++k) {
+    __syncthreads();
+    const uint32_t half = FFT_N >> (k + 1), b = t / half, u = b * 2 * half + t % half, v = u + half;
+    const double4 w = dd_tw[(1 << k) + b];
+    const DD wr{w.x, w.y}, wi{w.z, w.w}, vr = s_re[v], vi = s_im[v], ur = s_re[u], ui = s_im[u];
+    const DD tr = dd_add(dd_mul(wr, vr), dd_neg(dd_mul(wi, vi))), ti = dd_add(dd_mul(wr, vi), dd_mul(wi, vr));
+    s_re[u] = dd_add(ur, tr);
+    s_im[u] = dd_add(ui, ti);
+    s_re[v] = dd_add(ur, dd_neg(tr));
+    s_im[v] = dd_add(ui, dd_neg(ti));
+  }
   __syncthreads();
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (uint32_t poly = blockIdx.x * WAVES + wave; poly < n_polys; poly += gridDim.x * WAVES) {
-    const uint32_t* src = bk_coeff + (size_t)poly * RING_N;
-    Poly2 v;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const uint32_t x = src[lay_a(lane, r)];
-      v.a[r] = x % P1;
-      v.b[r] = x % P2;
-    }
-    ntt_fwd(v, s_buf[wave], s_tw, tw_fwd, lane);
-    uint32_t* dst = bk_ntt + (size_t)poly * 2 * RING_N;  // plane of P1, then plane of P2
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      // Canonical residues of the lazy signed forward output (|v| < 16P), once per key.
-      const uint32_t a = (uint32_t)((int32_t)v.a[r] + 16 * (int32_t)P1) % P1;
-      const uint32_t b = (uint32_t)((int32_t)v.b[r] + 16 * (int32_t)P2) % P2;
-      dst[r * 64 + lane] = csub(shoup(a, scale.x, scale.y, P1), P1);
-      dst[RING_N + r * 64 + lane] = csub(shoup(b, scale.z, scale.w, P2), P2);
-    }
+  // Rows in the order a step reads them: digit 0 of A, digit 0 of B, digit 1 of A, ...
+  const uint32_t i_row = row / (2 * ELL), r = row % (2 * ELL);
+  double2* out = bk_fft + ((size_t)(i_row * 2 * ELL + (r % ELL) * 2 + r / ELL) * FFT_CHANNELS + ch) * FFT_N;
+  for (uint32_t i = t; i < FFT_N; i += 256) {
+    const uint32_t lane = (i >> 5) | ((i & 8) << 1) | ((i & 16) << 1), m = ((i & 3) << 1) | ((i >> 2) & 1);
+    out[m * 64 + lane] = make_double2(s_re[i].h * (1.0 / FFT_N), s_im[i].h * (1.0 / FFT_N));
   }
 }
 
@@ -70,510 +106,579 @@ __global__ void ksk_relayout_kernel(const uint32_t* __restrict__ in, uint32_t* _
 }
 
 // ---------------------------------------------------------------------------
-// Blind rotation + sample extraction, one wavefront per item.
+// Blind rotation + sample extraction, one wavefront per rotation
+// (br1_kernel): the whole CMux in one wavefront, so its steps need no
+// workgroup barrier.  Bound: double-precision FMA issue.  Per step and
+// wavefront about 3,750 VALU instructions (288 of them lane swaps that take
+// two issue slots): 6 forward and 3 inverse 512-point transforms (216 and 288
+// FMAs or adds per lane), 576 product FMAs, 330 for rotation and digits, 224
+// for rounding and recombination.  256 VGPRs, two wavefronts per SIMD, 8
+// rotations per CU.
+// Beside the VALU (16.2k of 23k clocks a step and wavefront at 8 rotations
+// per CU) the step moves 147 KB of key through the vector L1 (64 B/clk) and
+// about 2k clocks of LDS traffic; both are kept in flight behind arithmetic
+// (eight key loads always outstanding, the exchange's real parts under way
+// while the imaginary ones are computed).
+// Measured (rotations only): 2,048 in 12.0 ms (171k/s; the two-prime NTT
+// kernel it replaces: 21.7 ms, 94k/s), 1,024 at 4 per CU in 7.5 ms (10.9 ms).
 // ---------------------------------------------------------------------------
+// The wavefronts of a workgroup read the same key: a barrier every few steps
+// keeps them close enough to share it in the L1 and L2.  Every step: 8.1 ms
+// for 1,024 rotations at 4 per CU; every 8: 7.5 ms; every 64: 12.4 ms for
+// 2,048 at 8 per CU instead of 12.0.
+constexpr int STEPS_PER_BARRIER = 8;
+
 constexpr uint32_t DEC_OFFSET = (1u << 31) + (1u << 24) + (1u << 17) + (1u << 10);
 // Balanced digit l of D (with DEC_OFFSET added) is its 7-bit field minus 64,
 // i.e. the field with bit 6 flipped read as a signed 7-bit number: flipping
 // those bits once per coefficient lets one signed bit-field extract give
 // each digit.
 constexpr uint32_t DIGIT_FLIP = (1u << 31) | (1u << 24) | (1u << 17);
-__device__ __forceinline__ uint32_t digit_of(uint32_t d_flipped, int shift) {
-  return (uint32_t)__builtin_amdgcn_sbfe((int)d_flipped, (unsigned)shift, (unsigned)BG_BIT);
+
+// Accumulator polynomial in LDS: rows of 32 coefficients behind one row that
+// holds the negated last row, so that coefficient j - ab of a lane that falls
+// off the front of row 0 is read there: the lanes of a row then share one sign.
+constexpr int ACC_WORDS = 33 * 32;
+
+// Gate pre-combination of word w and its modulus switch.
+__device__ __forceinline__ uint32_t abar_of(const BrItem& I, uint32_t w) {
+  uint32_t x = (uint32_t)I.ca * ((const g_u32*)I.a)[w];
+  if (I.b) x += (uint32_t)I.cb * ((const g_u32*)I.b)[w];
+  for (uint32_t t = 0; t < I.n_more; ++t) x += (uint32_t)I.cm * ((const g_u32*)I.more[t])[w];
+  if (w == (uint32_t)LWE_n) x += I.cst;
+  return (x + (1u << 20)) >> 21;
 }
 
-// Global-address-space views: loads through them are global (not flat)
-// loads, so they are not counted by the LDS wait of the transposes.
-typedef const uint32_t __attribute__((address_space(1))) g_u32;
 
-// Up to 4 wavefronts per workgroup (one per SIMD) a wavefront may hold 512
-// registers: the key rows are prefetched and the accumulators are 64-bit.
-// With 8 (two per SIMD, so one hides the other's latencies) it has 256: the
-// key is read where it is used and the accumulators are 32-bit.
-template <int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void br_kernel(const BrItem* __restrict__ items, uint32_t count,
-                                                         const Tw* __restrict__ tw_fwd) {
-  constexpr bool kPrefetchKey = WAVES <= 4, kWideAcc = WAVES <= 4;
-  using Acc = typename std::conditional<kWideAcc, int64_t, uint32_t>::type;
-  __shared__ Tw s_tw[RING_N];                   // twiddles of both primes (16 KB)
-  __shared__ uint2 s_buf[WAVES][RING_N];        // per-wave transpose scratch
-  __shared__ uint32_t s_acc[WAVES][2][RING_N];  // per-wave accumulator (A, B), coefficient order
-  __shared__ uint16_t s_abar[WAVES][CT_n + 1];  // modulus-switched input
-  for (int k = threadIdx.x; k < RING_N; k += blockDim.x) s_tw[k] = tw_fwd[k];
-  __syncthreads();
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  uint2* buf = s_buf[wave];
-  uint32_t* acc = s_acc[wave][0];
-  uint16_t* abar = s_abar[wave];
-
-  for (uint32_t it = blockIdx.x * WAVES + wave; it < count; it += gridDim.x * WAVES) {
-    const BrItem I = items[it];
-    // Gate pre-combination and modulus switch of all 631 words.
-    wave_lds_sync();
-    const g_u32* in_a = (const g_u32*)I.a;
-    const g_u32* in_b = (const g_u32*)I.b;
-    for (int w = lane; w < CT_n; w += 64) {
-      uint32_t x = (uint32_t)I.ca * in_a[w];
-      if (I.b) x += (uint32_t)I.cb * in_b[w];
-      for (uint32_t t = 0; t < I.n_more; ++t) x += (uint32_t)I.cm * ((const g_u32*)I.more[t])[w];
-      if (w == LWE_n) x += I.cst;
-      abar[w] = (uint16_t)((x + (1u << 20)) >> 21);
-    }
-    wave_lds_sync();
-    // acc = (0, X^(-bbar) * mu * (1 + X + ... + X^1023)); coefficient j = 64 r + lane.
-    const uint32_t bbar = __builtin_amdgcn_readfirstlane(abar[LWE_n]);
-    const uint32_t rot = (2048u - bbar) & 2047u;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const uint32_t j = r * 64 + lane;
-      const bool neg = (j < (rot & 1023u)) != (rot >= 1024u);
-      acc[j] = 0;
-      acc[RING_N + j] = neg ? (0u - I.mu) : I.mu;
-    }
-    const uint32_t* bk_i = I.bk;
-    for (int i = 0; i < LWE_n; ++i, bk_i += BK_ROW_WORDS) {
-      const uint32_t ab = __builtin_amdgcn_readfirstlane((uint32_t)abar[i]);
-      if (ab == 0) continue;
-      // External product BK_i x (X^ab acc - acc): the six digit polynomials are
-      // transformed one at a time and multiplied into the accumulators.
-      //  - wide (64-bit) accumulators take the lazy signed transform values
-      //    (|x| < 16P): one Montgomery reduction of the six products at the
-      //    end gives (-4P, 4P);
-      //  - narrow (32-bit) accumulators reduce each product (|x b| < 16P^2)
-      //    into (-5P/4, P/4 + 1) and sum the six lazily.
-      Acc m0a[16], m0b[16], m1a[16], m1b[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) m0a[r] = m0b[r] = m1a[r] = m1b[r] = 0;
-      wave_lds_sync();  // accumulator updates of the previous step are visible
-#pragma unroll 1
-      for (int c = 0; c < 2; ++c) {
-        const uint32_t* poly = acc + c * RING_N;
-        // D = X^ab p - p, plus the rounding offset of the decomposition.  All 32
-        // reads are issued before the first use (one LDS round trip).
-        uint32_t D[16], src[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const uint32_t j = r * 64 + lane;
-          src[r] = poly[((j + 2048u - ab) & 2047u) & 1023u];  // coefficient j of X^ab p is +-p[j - ab]
-          D[r] = poly[j];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const uint32_t s = (r * 64 + lane + 2048u - ab) & 2047u;
-          D[r] = ((s >= 1024u ? 0u - src[r] : src[r]) - D[r] + DEC_OFFSET) ^ DIGIT_FLIP;
-        }
-#pragma unroll 1
-        for (int lev = 0; lev < ELL; ++lev) {
-          // Residues mod P1 and mod P2 of the two key rows of this digit (planes
-          // of 1,024 words: row 0 P1, row 0 P2, row 1 P1, row 1 P2); with
-          // registers to spare they are requested before the transform, which
-          // hides their latency.
-          const g_u32* k0 = (const g_u32*)(bk_i + (size_t)((c * ELL + lev) * 4) * RING_N);
-          uint32_t b0a[16], b0b[16], b1a[16], b1b[16];
-          if constexpr (kPrefetchKey) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              b0a[r] = k0[r * 64 + lane];
-              b0b[r] = k0[RING_N + r * 64 + lane];
-              b1a[r] = k0[2 * RING_N + r * 64 + lane];
-              b1b[r] = k0[3 * RING_N + r * 64 + lane];
-            }
-          }
-          const int shift = 32 - BG_BIT * (lev + 1);
-          Poly2 v;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) v.a[r] = v.b[r] = digit_of(D[r], shift);  // signed, |d| <= 64
-          ntt_fwd(v, buf, s_tw, tw_fwd, lane);
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            if constexpr (!kPrefetchKey) {
-              b0a[r] = k0[r * 64 + lane];
-              b0b[r] = k0[RING_N + r * 64 + lane];
-              b1a[r] = k0[2 * RING_N + r * 64 + lane];
-              b1b[r] = k0[3 * RING_N + r * 64 + lane];
-            }
-            const int64_t da = (int32_t)v.a[r], db = (int32_t)v.b[r];  // |x| < 16P
-            if constexpr (kWideAcc) {
-              m0a[r] += da * (int32_t)b0a[r];
-              m0b[r] += db * (int32_t)b0b[r];
-              m1a[r] += da * (int32_t)b1a[r];
-              m1b[r] += db * (int32_t)b1b[r];
-            } else {
-              m0a[r] += redc_s(da * (int32_t)b0a[r], P1, P1_INV);
-              m0b[r] += redc_s(db * (int32_t)b0b[r], P2, P2_INV);
-              m1a[r] += redc_s(da * (int32_t)b1a[r], P1, P1_INV);
-              m1b[r] += redc_s(db * (int32_t)b1b[r], P2, P2_INV);
-            }
-          }
-        }
-      }
-#pragma unroll 1
-      for (int c = 0; c < 2; ++c) {
-        Poly2 v;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          if constexpr (kWideAcc) {  // (-4P, 4P), the inverse transform's input range
-            v.a[r] = redc_s(c ? m1a[r] : m0a[r], P1, P1_INV);
-            v.b[r] = redc_s(c ? m1b[r] : m0b[r], P2, P2_INV);
-          } else {  // |sum| < 7.5P -> (-P/2, 3P/2)
-            v.a[r] = reduce_s(c ? m1a[r] : m0a[r], P1);
-            v.b[r] = reduce_s(c ? m1b[r] : m0b[r], P2);
-          }
-        }
-        ntt_inv(v, buf, s_tw, tw_fwd, lane);
-        uint32_t* poly = acc + c * RING_N;
-        uint32_t old[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) old[r] = poly[r * 64 + lane];
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) poly[r * 64 + lane] = old[r] + crt_lift_s(v.a[r], v.b[r]);
-      }
-    }
-    wave_lds_sync();
-    // SampleExtract: a'_0 = A_0, a'_j = -A_(N-j), b' = B_0.
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int j = r * 64 + lane;
-      const uint32_t a = acc[j];
-      if (j == 0) I.out[0] = a;
-      else I.out[RING_N - j] = 0u - a;
-    }
-    if (lane == 0) I.out[RING_N] = acc[RING_N];
-  }
+// Products of one transformed digit polynomial of each accumulator half with
+// its three key channels, added to (FIRST: starting) the sums.
+// The key is one stream of batches of 8 values per lane (one transformed
+// digit polynomial's products with one channel), read in order; v holds the
+// batch that comes next.  Each value is replaced by the one of the batch after
+// as soon as it is used, so eight loads are always in flight, also while the
+// next digit is transformed.
+typedef int v4i __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void key_load(double2 (&v)[8], __amdgpu_buffer_rsrc_t key, int lane16, int off, int m) {
+  const v4i w = __builtin_amdgcn_raw_buffer_load_b128(key, lane16 + (m & 3) * 1024, off + (m >> 2) * 4096, 0);
+  v[m] = __builtin_bit_cast(double2, w);
 }
-
-// ---------------------------------------------------------------------------
-// Blind rotation split by prime: a workgroup of two wavefronts per item, wave
-// PR computing every product modulo prime PR.  Each wavefront needs about half
-// the registers of the one-wavefront form, so two fit on a SIMD and hide each
-// other's memory and LDS latency.  Per CMux the two meet twice: after the
-// inverse transforms (each hands the other the residues of the output
-// polynomial that the other lifts) and after the accumulator update.
-// ---------------------------------------------------------------------------
-// SKIP: steps with abar_i = 0 (X^0 acc - acc = 0, an exact no-op) are skipped;
-// workgroups holding several rotations run them all, so that every wavefront
-// of the workgroup meets the same barriers.
-template <int PR, bool SKIP>
-__device__ __forceinline__ void br2_rotate(const BrItem& I, uint32_t* acc, const uint16_t* abar, uint32_t* buf,
-                                           uint32_t* buf2, const uint32_t* other_buf, const uint2* tws, int lane) {
-  constexpr uint32_t P = Prime<PR>::P, PINV = Prime<PR>::PINV;
-  const uint32_t* bk_i = I.bk;
-  for (int i = 0; i < LWE_n; ++i, bk_i += BK_ROW_WORDS) {
-    const uint32_t ab = __builtin_amdgcn_readfirstlane((uint32_t)abar[i]);
-    if (SKIP && ab == 0) continue;  // the same decision in both wavefronts: abar is shared
-    // Signed 64-bit accumulators of the two output polynomials mod P: six
-    // products of transform values (|x| < 16P) and key residues (< P); one
-    // reduction at the end gives (-4P, 4P), the inverse transform's input range.
-    int64_t m0[16], m1[16];
+// s += a * v for one channel; NEXT: replaces v by the batch at offset off.
+template <bool NEXT>
+__device__ __forceinline__ void key_products(Cplx (&s)[8], const Cplx (&a)[8], double2 (&v)[8],
+                                             __amdgpu_buffer_rsrc_t key, int lane16, int off) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) m0[r] = m1[r] = 0;
-#pragma unroll 1
-    for (int c = 0; c < 2; ++c) {
-      // Polynomial c and its negation side by side (2048 words): coefficient
-      // j of X^ab p is word (j - ab) mod 2048 of that window.
-      const uint32_t* poly = acc + c * 2 * RING_N;
-      uint32_t D[16], src[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const uint32_t j = r * 64 + lane;
-        src[r] = poly[(j + 2048u - ab) & 2047u];
-        D[r] = poly[j];
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) D[r] = (src[r] - D[r] + DEC_OFFSET) ^ DIGIT_FLIP;
-      // Unrolled: a quarter fewer scalar instructions per polynomial (the
-      // loop's control and key addressing) and scheduling across the digits;
-      // 1.1% less time per launch than a loop.
-#pragma unroll
-      for (int lev = 0; lev < ELL; ++lev) {
-        // This prime's planes of the two key rows of the digit, requested
-        // before the transform so that it hides their latency.
-        const g_u32* k0 = (const g_u32*)(bk_i + (size_t)((c * ELL + lev) * 4 + PR) * RING_N);
-        uint32_t b0[16], b1[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          b0[r] = k0[r * 64 + lane];
-          b1[r] = k0[2 * RING_N + r * 64 + lane];
-        }
-        const int shift = 32 - BG_BIT * (lev + 1);
-        uint32_t x[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) x[r] = digit_of(D[r], shift);  // balanced digit, signed
-        ntt_fwd1<PR>(x, buf, tws, lane);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          m0[r] += (int64_t)(int32_t)x[r] * (int32_t)b0[r];
-          m1[r] += (int64_t)(int32_t)x[r] * (int32_t)b1[r];
-        }
-      }
-    }
-    // Wave 0 lifts output 0 (A), wave 1 output 1 (B).  The kept output is
-    // transformed first and stays in registers; the other one is transformed
-    // next and parked in this wavefront's LDS buffer for the partner.
-    constexpr int KEEP = PR;
-    uint32_t keep[16], x[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      keep[r] = redc_s(KEEP ? m1[r] : m0[r], P, PINV);
-      x[r] = redc_s(KEEP ? m0[r] : m1[r], P, PINV);
-    }
-    ntt_inv1_pair<PR>(keep, x, buf, buf2, tws, lane);  // both end below 16P: the lift takes lazy residues
-    wave_lds_sync();  // the transform's last reads of buf are done
-#pragma unroll
-    for (int r = 0; r < 16; ++r) buf[r * 64 + lane] = x[r];
-    __syncthreads();  // both wavefronts have parked their residues
-    uint32_t* poly = acc + KEEP * 2 * RING_N;
-    uint32_t old[16], oth[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      old[r] = poly[r * 64 + lane];
-      oth[r] = other_buf[r * 64 + lane];
-    }
+  for (int m = 0; m < 8; ++m) {
+    s[m].r = __builtin_fma(a[m].r, v[m].x, s[m].r);
+    s[m].i = __builtin_fma(a[m].r, v[m].y, s[m].i);
+    s[m].r = __builtin_fma(-a[m].i, v[m].y, s[m].r);
+    s[m].i = __builtin_fma(a[m].i, v[m].x, s[m].i);
+    if (NEXT) key_load(v, key, lane16, off, m);
     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const uint32_t v = old[r] + (PR == 0 ? crt_lift_s(keep[r], oth[r]) : crt_lift_s(oth[r], keep[r]));
-      poly[r * 64 + lane] = v;
-      poly[RING_N + r * 64 + lane] = 0u - v;
-    }
-    __syncthreads();  // accumulator updated; parked residues consumed
   }
 }
 
-// ROT rotations per workgroup (2 * ROT wavefronts): with ROT > 1 the
-// rotations of a workgroup advance in lockstep (their wavefronts share every
-// barrier), so they read each key row at the same time; a partial last
-// workgroup repeats the last item in its idle rotations and writes nothing.
 template <int ROT>
-__global__ __launch_bounds__(128 * ROT) __attribute__((amdgpu_waves_per_eu(2))) void br2_kernel(
-    const BrItem* __restrict__ items, uint32_t count, const Tw* __restrict__ tw_fwd) {
-  __shared__ uint2 s_tw[2][RING_N];              // per prime: {w, Shoup(w)}, stage slices permuted (16 KB)
-  __shared__ __align__(16) uint32_t s_buf[2 * ROT][RING_N];  // per wavefront: transpose scratch, then parked residues
-  __shared__ __align__(16) uint32_t s_buf2[2 * ROT][RING_N]; // per wavefront: second transpose scratch
-  __shared__ uint32_t s_acc[ROT][2][2 * RING_N];  // per rotation: accumulator A, -A, B, -B, coefficient order
-  __shared__ uint16_t s_abar[ROT][CT_n + 1];     // per rotation: modulus-switched input
-  for (int e = 16 + threadIdx.x; e < RING_N; e += blockDim.x) {  // stages 4..9 (entries 16..1023)
-    const int S = 31 - __builtin_clz(e);
-    const int slot = (1 << S) + tw_perm(S, e - (1 << S));
-    const Tw w = tw_fwd[e];
-    s_tw[0][slot] = make_uint2(w.x, w.y);
-    s_tw[1][slot] = make_uint2(w.z, w.w);
-  }
-  const int lane = threadIdx.x & 63;
+__global__ __launch_bounds__(64 * ROT) __attribute__((amdgpu_waves_per_eu(2))) void br1_kernel(
+    const BrItem* __restrict__ items, uint32_t count, const double2* __restrict__ lane_tw) {
+  __shared__ uint32_t s_acc[ROT][2 * ACC_WORDS];
+  __shared__ double s_x[ROT][2 * XPOLY];
+  __shared__ double2 s_tw[LANE_TW][64];
+  for (int e = threadIdx.x; e < LANE_TW * 64; e += 64 * ROT) s_tw[0][e] = lane_tw[e];
+  __syncthreads();
+  const int lane = threadIdx.x & 63, c = lane >> 5, l = lane & 31, rho = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int rot_i = wave >> 1, pr = wave & 1, t = threadIdx.x & 127;  // t: thread within the rotation's pair
-  // Wavefront w runs on SIMD w mod 4, so each SIMD holds rotation r and
-  // rotation r + 2 of the same prime, which reach their LDS waits together.
-  // Raising the first one's issue priority lets it run ahead until it waits
-  // while the other fills the gaps (12.21 -> 12.12 ms per launch).
-  if (ROT == 4 && rot_i < 2) __builtin_amdgcn_s_setprio(1);
-  uint32_t* acc = s_acc[rot_i][0];
-  uint16_t* abar = s_abar[rot_i];
-  for (uint32_t g = blockIdx.x; g * ROT < count; g += gridDim.x) {
-    const uint32_t idx = g * ROT + rot_i;
-    const bool active = idx < count;
-    const BrItem I = items[active ? idx : count - 1];
-    __syncthreads();  // the previous item's readers of acc and abar are done
-    const g_u32* in_a = (const g_u32*)I.a;
-    const g_u32* in_b = (const g_u32*)I.b;
-    for (int w = t; w < CT_n; w += 128) {
-      uint32_t x = (uint32_t)I.ca * in_a[w];
-      if (I.b) x += (uint32_t)I.cb * in_b[w];
-      for (uint32_t k = 0; k < I.n_more; ++k) x += (uint32_t)I.cm * ((const g_u32*)I.more[k])[w];
-      if (w == LWE_n) x += I.cst;
-      abar[w] = (uint16_t)((x + (1u << 20)) >> 21);
-    }
-    __syncthreads();
-    // acc = (0, X^(-bbar) * mu * (1 + X + ... + X^1023)): wave 0 of the pair writes A, wave 1 B.
-    const uint32_t bbar = __builtin_amdgcn_readfirstlane(abar[LWE_n]);
+  const uint32_t idx = blockIdx.x * ROT + wave;
+  if (idx >= count) {  // no rotation: only meets the others at their barriers
+    for (int i = 0; i < LWE_n; i += STEPS_PER_BARRIER) __builtin_amdgcn_s_barrier();
+    return;
+  }
+  const BrItem I = items[idx];
+  uint32_t* acc = s_acc[wave] + c * ACC_WORDS + 32 + l;  // this lane's column of its polynomial
+  const double2* tw = &s_tw[0][lane];
+  double* xw = s_x[wave] + c * XPOLY + l;                 // layout 1 side of the exchange
+  double* xr = s_x[wave] + XROW * rho + ((lane >> 5) << 1) + ((lane >> 4) & 1);  // layout 2 side
+  // acc = (0, X^(-bbar) * mu * (1 + X + ... + X^1023)).
+  {
+    const uint32_t bbar = __builtin_amdgcn_readfirstlane(abar_of(I, LWE_n));
     const uint32_t rot = (2048u - bbar) & 2047u;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const uint32_t j = r * 64 + lane;
+    for (int R = 0; R < 32; ++R) {
+      const uint32_t j = 32 * R + l;
       const bool neg = (j < (rot & 1023u)) != (rot >= 1024u);
-      const uint32_t v = pr == 0 ? 0u : (neg ? (0u - I.mu) : I.mu);
-      acc[pr * 2 * RING_N + j] = v;
-      acc[pr * 2 * RING_N + RING_N + j] = 0u - v;
-    }
-    __syncthreads();
-    if (pr == 0)
-      br2_rotate<0, ROT == 1>(I, acc, abar, s_buf[2 * rot_i], s_buf2[2 * rot_i], s_buf[2 * rot_i + 1], s_tw[0], lane);
-    else
-      br2_rotate<1, ROT == 1>(I, acc, abar, s_buf[2 * rot_i + 1], s_buf2[2 * rot_i + 1], s_buf[2 * rot_i], s_tw[1], lane);
-    // SampleExtract: a'_0 = A_0, a'_j = -A_(N-j), b' = B_0 (the last update is
-    // visible after the rotation's closing barrier, or the one above if no step ran).
-    if (active) {
-      for (int j = t; j < RING_N; j += 128) I.out[j] = j == 0 ? acc[0] : acc[2 * RING_N - j];  // -A_(N-j)
-      if (t == 0) I.out[RING_N] = acc[2 * RING_N];
+      const uint32_t v = c == 0 ? 0u : (neg ? (0u - I.mu) : I.mu);
+      acc[32 * R] = v;
+      if (R == 31) acc[-32] = 0u - v;
     }
   }
-}
-
-// ---------------------------------------------------------------------------
-// Blind rotation split by prime and by accumulator half: a workgroup of four
-// wavefronts per item; wave w = PR + 2H computes, modulo prime PR, the three
-// digit polynomials of accumulator polynomial H and its products with the key
-// rows for both outputs.  Per CMux each wavefront runs 3 forward and 1 inverse
-// transform (half the split form's), so one rotation takes about half as
-// long; three workgroup barriers per CMux:
-//   B1  partial sums: wave (PR, H) receives from (PR, 1-H) the partial of
-//       output H over the other three digits, adds it to its own and runs the
-//       inverse transform of output H modulo PR;
-//   B2  CRT: waves (0, H) and (1, H) swap half of their residues, each lifts
-//       8 of the 16 registers of output H and updates the accumulator;
-//   B3  the accumulator is complete for the next CMux.
-// ---------------------------------------------------------------------------
-template <int PR, int H>
-__device__ __forceinline__ void br4_rotate(const BrItem& I, uint32_t* acc, const uint16_t* abar, uint32_t* buf,
-                                           const uint32_t* prime_partner_buf, uint32_t* xbuf,
-                                           const uint32_t* half_partner_xbuf, const uint2* tws,
-                                           int lane) {
-  constexpr uint32_t P = Prime<PR>::P, PINV = Prime<PR>::PINV;
-  const uint32_t* bk_i = I.bk;
-  for (int i = 0; i < LWE_n; ++i, bk_i += BK_ROW_WORDS) {
-    const uint32_t ab = __builtin_amdgcn_readfirstlane((uint32_t)abar[i]);
-    if (ab == 0) continue;  // the same decision in all four wavefronts: abar is shared
-    // Three products of transform values (|x| < 16P) and key residues (< P)
-    // per output: one reduction gives (-2P, 2P).
-    int64_t m0[16], m1[16];
+  const double magic = 6755399441055744.0;  // 1.5 * 2^52: the sum's low words are the nearest integer
+  const double magic_lo = magic + (c ? (double)(1 << (LO_SHIFT - 1)) : 0.0);
+  uint32_t lo_shift = c ? LO_SHIFT : 0;
+  asm("" : "+v"(lo_shift));  // one funnel shift by a register, not a shift and a select
+  uint32_t own[32];  // this lane's accumulator coefficients
 #pragma unroll
-    for (int r = 0; r < 16; ++r) m0[r] = m1[r] = 0;
+  for (int R = 0; R < 32; ++R) own[R] = acc[32 * R];
+  uint32_t abars = 0;
+  const __amdgpu_buffer_rsrc_t key =
+      __builtin_amdgcn_make_buffer_rsrc((void*)I.bk, 0, (int)BK_FFT_BYTES, 0x00027000);
+  const int lane16 = lane * 16;
+  int off = 0;
+  double2 v[8];
+#pragma unroll
+  for (int m = 0; m < 8; ++m) key_load(v, key, lane16, off, m);
+  for (int i = 0; i < LWE_n; ++i) {
+    if (i % STEPS_PER_BARRIER == 0) __builtin_amdgcn_s_barrier();
+    if ((i & 63) == 0) abars = i + lane < LWE_n ? abar_of(I, i + lane) : 0u;
+    const uint32_t ab = __builtin_amdgcn_readlane(abars, i & 63);
+    const int abh = (int)(ab >> 5), abl = (int)(ab & 31);
+    uint32_t D[32];
+    wave_lds_sync();  // the accumulator updates of the last step
     {
-      const uint32_t* poly = acc + H * RING_N;
-      uint32_t D[16], src[16];
+      const uint32_t* src = acc - abl;
+      uint32_t w[32];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const uint32_t j = r * 64 + lane;
-        src[r] = poly[((j + 2048u - ab) & 2047u) & 1023u];  // coefficient j of X^ab p is +-p[j - ab]
-        D[r] = poly[j];
+      for (int R = 0; R < 32; ++R) w[R] = src[((R - abh) & 31) * 32];
+#pragma unroll
+      for (int R = 0; R < 32; ++R) {
+        const uint32_t mask = 0u - (uint32_t)(((R - abh) >> 5) & 1);
+        D[R] = ((w[R] ^ mask) + ((DEC_OFFSET - mask) - own[R])) ^ DIGIT_FLIP;
       }
+    }
+    Cplx s[FFT_CHANNELS][8];
+#pragma unroll
+    for (int ch = 0; ch < FFT_CHANNELS; ++ch)
+#pragma unroll
+      for (int m = 0; m < 8; ++m) s[ch][m] = {0.0, 0.0};
+    // The second and third digits of two coefficients share a word, which
+    // halves the registers they occupy while the first is worked on.
+    uint32_t P[16];
+    auto digit = [&](auto first_t, unsigned shift) {
+      constexpr bool first = decltype(first_t)::value;
+      Cplx z[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        if constexpr (first) {
+          z[q].r = (double)((int)D[q] >> 25);
+          z[q].i = (double)((int)D[16 + q] >> 25);
+          P[q] = ((D[q] >> 9) & 0xFFFFu) | ((D[16 + q] << 7) & 0xFFFF0000u);
+        } else {
+          z[q].r = (double)(int)__builtin_amdgcn_sbfe(P[q], shift, (unsigned)BG_BIT);
+          z[q].i = (double)(int)__builtin_amdgcn_sbfe(P[q], shift + 16, (unsigned)BG_BIT);
+        }
+      }
+      fwd_stage1<0>(z);
+      fwd_stage1<1>(z);
+      fwd_stage1<2>(z);
+      // Stage 3 and the exchange of its outputs, real parts first: they are on
+      // their way while the imaginary parts are computed.
+      Cplx a[8], b[8];
+      wave_lds_sync();
+#pragma unroll
+      for (int q = 0; q < 16; q += 2) {
+        const double wr = W_RE[w_index(3, q >> 1)], wi = W_IM[w_index(3, q >> 1)];
+        const Cplx &u = z[q], &w = z[q + 1];
+        const double x = (q >> 1) & 1 ? __builtin_fma(-wr, w.i, __builtin_fma(-wi, w.r, u.r))
+                                      : __builtin_fma(wr, w.r, __builtin_fma(-wi, w.i, u.r));
+        xw[XROW * q] = x;
+        xw[XROW * (q + 1)] = __builtin_fma(2.0, u.r, -x);
+      }
+      wave_lds_sync();
+#pragma unroll
+      for (int m = 0; m < 8; ++m) a[m].r = xr[4 * m];
+#pragma unroll
+      for (int m = 0; m < 8; ++m) b[m].r = xr[XPOLY + 4 * m];
+      wave_lds_sync();
+#pragma unroll
+      for (int q = 0; q < 16; q += 2) {
+        const double wr = W_RE[w_index(3, q >> 1)], wi = W_IM[w_index(3, q >> 1)];
+        const Cplx &u = z[q], &w = z[q + 1];
+        const double x = (q >> 1) & 1 ? __builtin_fma(wr, w.r, __builtin_fma(-wi, w.i, u.i))
+                                      : __builtin_fma(wr, w.i, __builtin_fma(wi, w.r, u.i));
+        xw[XROW * q] = x;
+        xw[XROW * (q + 1)] = __builtin_fma(2.0, u.i, -x);
+      }
+      wave_lds_sync();
+      // A wavefront's LDS reads return in issue order: the twiddles first.
+      const TwA ta = load_twa(tw);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const uint32_t s = (r * 64 + lane + 2048u - ab) & 2047u;
-        D[r] = ((s >= 1024u ? 0u - src[r] : src[r]) - D[r] + DEC_OFFSET) ^ DIGIT_FLIP;
-      }
-      // Unrolled as in br2_rotate (5.5% less time per launch than a loop).
+      for (int m = 0; m < 8; ++m) a[m].i = xr[4 * m];
+      const TwB tb = load_twb(tw);
 #pragma unroll
-      for (int lev = 0; lev < ELL; ++lev) {
-        const g_u32* k0 = (const g_u32*)(bk_i + (size_t)((H * ELL + lev) * 4 + PR) * RING_N);
-        uint32_t b0[16], b1[16];
+      for (int m = 0; m < 8; ++m) b[m].i = xr[XPOLY + 4 * m];
+      __builtin_amdgcn_sched_barrier(0);
+      fwd_stages456(a, ta);
+      swap_23(a);
+      fwd_stages78(a, tb);
+      __builtin_amdgcn_sched_barrier(0);
+      key_products<true>(s[0], a, v, key, lane16, off + 1 * 8192);
+      fwd_stages456(b, ta);
+      __builtin_amdgcn_sched_barrier(0);
+      key_products<true>(s[1], a, v, key, lane16, off + 2 * 8192);
+      swap_23(b);
+      __builtin_amdgcn_sched_barrier(0);
+      key_products<true>(s[2], a, v, key, lane16, off + 3 * 8192);
+      double2 w[8];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          b0[r] = k0[r * 64 + lane];
-          b1[r] = k0[2 * RING_N + r * 64 + lane];
-        }
-        const int shift = 32 - BG_BIT * (lev + 1);
-        uint32_t x[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) x[r] = digit_of(D[r], shift);  // balanced digit, signed
-        ntt_fwd1<PR>(x, buf, tws, lane);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          m0[r] += (int64_t)(int32_t)x[r] * (int32_t)b0[r];
-          m1[r] += (int64_t)(int32_t)x[r] * (int32_t)b1[r];
-        }
-      }
-    }
-    // Hand the partial of output 1-H to the other half; keep output H's.
-    uint32_t x[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      xbuf[r * 64 + lane] = redc_s(H ? m0[r] : m1[r], P, PINV);  // (-2P, 2P)
-      x[r] = redc_s(H ? m1[r] : m0[r], P, PINV);
-    }
-    // The first two inverse stages' twiddles, read before the partner's
-    // products so that they are not queued behind those reads.
-    InvTw98 itw;
-    inv_tw98_load(itw, tws, lane);
-    __syncthreads();  // B1
-    uint32_t oth[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) oth[r] = half_partner_xbuf[r * 64 + lane];
+      for (int m = 0; m < 8; ++m) key_load(w, key, lane16, off + 4 * 8192, m);
+      __builtin_amdgcn_sched_barrier(0);
+      fwd_stages78(b, tb);
+      __builtin_amdgcn_sched_barrier(0);
+      key_products<true>(s[0], b, v, key, lane16, off + 5 * 8192);
+      key_products<false>(s[1], b, w, key, lane16, 0);
+      off += 6 * 8192;
+      key_products<true>(s[2], b, v, key, lane16, off);
+    };
+    digit(std::true_type(), 0);
+#pragma unroll 1
+    for (int shift = 9; shift > 0; shift -= 7) digit(std::false_type(), (unsigned)shift);
+    // Inverse transforms; each exchange's reads are in flight while the other
+    // channels are worked on.
+    TwB tb = load_twb(tw);
     __builtin_amdgcn_sched_barrier(0);
+    TwA ta = load_twa(tw);
+    __builtin_amdgcn_sched_barrier(0);
+    inv_stages87(s[0], tb);
+    inv_stages87(s[1], tb);
+    __builtin_amdgcn_sched_barrier(0);
+    swap_23(s[0]);
+    swap_23(s[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    inv_stages654(s[0], ta);
+    inv_stages654(s[1], ta);
+    __builtin_amdgcn_sched_barrier(0);
+    Cplx h[16], z[16];
+    wave_lds_sync();
 #pragma unroll
-    for (int r = 0; r < 16; ++r) x[r] += oth[r];  // (-4P, 4P)
-    ntt_inv1<PR>(x, itw, buf, tws, lane);
-    // Wave (0, H) lifts registers 0..7, wave (1, H) registers 8..15: each parks
-    // the half the other one lifts.
-    wave_lds_sync();  // the transform's last reads of buf are done
-    constexpr int MINE = PR * 8, THEIRS = 8 - PR * 8;
+    for (int m = 0; m < 8; ++m) xr[4 * m] = s[0][m].r;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) buf[(THEIRS + r) * 64 + lane] = x[THEIRS + r];  // lazy: the lift takes |x| < 16P
-    __syncthreads();  // B2
-    uint32_t* poly = acc + H * RING_N;
-    uint32_t old[8], o2[8];
+    for (int m = 0; m < 8; ++m) xr[XPOLY + 4 * m] = s[1][m].r;
+    wave_lds_sync();
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      old[r] = poly[(MINE + r) * 64 + lane];
-      o2[r] = prime_partner_buf[(MINE + r) * 64 + lane];
+    for (int q = 0; q < 16; ++q) h[q].r = xw[XROW * q];
+    wave_lds_sync();
+#pragma unroll
+    for (int m = 0; m < 8; ++m) xr[4 * m] = s[0][m].i;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) xr[XPOLY + 4 * m] = s[1][m].i;
+    wave_lds_sync();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) h[q].i = xw[XROW * q];
+    __builtin_amdgcn_sched_barrier(0);
+    inv_stages87(s[2], tb);
+    swap_23(s[2]);
+    inv_stages654(s[2], ta);
+    __builtin_amdgcn_sched_barrier(0);
+    const double* xp = s_x[wave] + l;  // the packed channel: both halves read the same values
+    wave_lds_sync();
+#pragma unroll
+    for (int m = 0; m < 8; ++m) xr[4 * m] = s[2][m].r;
+    wave_lds_sync();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) z[q].r = xp[XROW * q];
+    wave_lds_sync();
+#pragma unroll
+    for (int m = 0; m < 8; ++m) xr[4 * m] = s[2][m].i;
+    wave_lds_sync();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) z[q].i = xp[XROW * q];
+#pragma unroll
+    for (int R = 0; R < 32; ++R) own[R] = acc[32 * R];
+    __builtin_amdgcn_sched_barrier(0);
+    inv_stage1<3>(h);
+    inv_stage1<2>(h);
+    inv_stage1<1>(h);
+    inv_stage1<0>(h);
+    uint32_t hi[32];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      hi[q] = (uint32_t)__builtin_bit_cast(uint64_t, h[q].r + magic);
+      hi[16 + q] = (uint32_t)__builtin_bit_cast(uint64_t, h[q].i + magic);
     }
     __builtin_amdgcn_sched_barrier(0);
+    inv_stage1<3>(z);
+    inv_stage1<2>(z);
+    inv_stage1<1>(z);
+    inv_stage1<0>(z);
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const uint32_t mine = x[MINE + r];
-      poly[(MINE + r) * 64 + lane] = old[r] + (PR == 0 ? crt_lift_s(mine, o2[r]) : crt_lift_s(o2[r], mine));
+    for (int R = 0; R < 32; ++R) {
+      const uint64_t w = __builtin_bit_cast(uint64_t, (R < 16 ? z[R & 15].r : z[R & 15].i) + magic_lo);
+      const uint32_t f = __builtin_amdgcn_alignbit((uint32_t)(w >> 32), (uint32_t)w, lo_shift);
+      const int32_t lo = __builtin_amdgcn_sbfe((int)f, 0u, (unsigned)LO_SHIFT);
+      static_assert(KEY_RADIX == 20, "20 h + lo = ((5 h) << 2) + lo in two shift-adds");
+      uint32_t h5 = (hi[R] << 2) + hi[R];
+      asm("" : "+v"(h5));  // not a 32-bit multiply
+      own[R] += (h5 << 2) + (uint32_t)lo;
+      acc[32 * R] = own[R];
     }
-    __syncthreads();  // B3
+    acc[-32] = 0u - own[31];
   }
+  wave_lds_sync();
+  // SampleExtract: a'_0 = A_0, a'_j = -A_(N-j), b' = B_0.
+  const uint32_t* A = s_acc[wave] + 32;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int j = 64 * r + lane;
+    const uint32_t a = A[j];
+    if (j == 0) I.out[0] = a;
+    else I.out[RING_N - j] = 0u - a;
+  }
+  if (lane == 0) I.out[RING_N] = A[ACC_WORDS];
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void br4_kernel(
-    const BrItem* __restrict__ items, uint32_t count, const Tw* __restrict__ tw_fwd) {
-  __shared__ uint2 s_tw[2][RING_N];      // per prime: {w, Shoup(w)}, stage slices permuted (16 KB)
-  __shared__ __align__(16) uint32_t s_buf[4][RING_N];  // per wavefront: transpose scratch, then CRT hand-over
-  __shared__ uint32_t s_x[4][RING_N];    // per wavefront: partial sum handed to the other half
-  __shared__ uint32_t s_acc[2][RING_N];  // accumulator (A, B), coefficient order
-  __shared__ uint16_t s_abar[CT_n + 1];  // modulus-switched input
-  for (int e = 16 + threadIdx.x; e < RING_N; e += blockDim.x) {  // stages 4..9 (entries 16..1023)
-    const int S = 31 - __builtin_clz(e);
-    const int slot = (1 << S) + tw_perm(S, e - (1 << S));
-    const Tw w = tw_fwd[e];
-    s_tw[0][slot] = make_uint2(w.x, w.y);
-    s_tw[1][slot] = make_uint2(w.z, w.w);
-  }
-  const int lane = threadIdx.x & 63;
+// ---------------------------------------------------------------------------
+// Blind rotation, three wavefronts per rotation (br3_kernel), for rounds of at
+// most two rotations per CU: wavefront j transforms digit j of both
+// accumulator halves, multiplies with its two key rows, hands the other
+// wavefronts their channels' partial sums through LDS and transforms channel j
+// (hi_A, hi_B, packed lo) back; the packed channel's integers go to the other
+// two through LDS.  Three barriers per step.  Bound: the latency of that
+// chain (about 1,300 VALU instructions, 6.8k of 11.7k clocks a step for a
+// rotation alone; the rest are LDS round trips and barriers).
+// One rotation per workgroup (RING = 3: registers for 24 key loads in
+// flight): 3.06 ms for one rotation, 3.3 ms for 256 (3.8 ms before, with four
+// wavefronts and two-prime transforms); RING = 1: 3.30 and 3.38.  Two per
+// workgroup share barriers and fill each other's gaps: 512 in 4.46 ms
+// (6.3 ms), 6.3 ms as two rounds of one.
+// ---------------------------------------------------------------------------
+template <int ROT, int RING>
+__global__ __launch_bounds__(192 * ROT) __attribute__((amdgpu_waves_per_eu(2))) void br3_kernel(
+    const BrItem* __restrict__ items, uint32_t count, const double2* __restrict__ lane_tw) {
+  constexpr int REGION = 2 * XPOLY;  // doubles: one polynomial's values (1,024 doubles), padded for the exchange
+  constexpr int REGIONS = 6;
+  __shared__ double s_x[ROT][REGIONS][REGION];
+  __shared__ double2 s_tw[LANE_TW][64];
+  __shared__ uint32_t s_acc[ROT][2][3 * RING_N];
+  for (int e = threadIdx.x; e < LANE_TW * 64; e += 192 * ROT) s_tw[0][e] = lane_tw[e];
+  const int lane = threadIdx.x & 63, c = lane >> 5, l = lane & 31, rho = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  uint32_t* acc = s_acc[0];
-  for (uint32_t it = blockIdx.x; it < count; it += gridDim.x) {
-    const BrItem I = items[it];
-    __syncthreads();  // the previous item's readers of acc and abar are done
-    const g_u32* in_a = (const g_u32*)I.a;
-    const g_u32* in_b = (const g_u32*)I.b;
-    for (int w = threadIdx.x; w < CT_n; w += 256) {
-      uint32_t x = (uint32_t)I.ca * in_a[w];
-      if (I.b) x += (uint32_t)I.cb * in_b[w];
-      for (uint32_t t = 0; t < I.n_more; ++t) x += (uint32_t)I.cm * ((const g_u32*)I.more[t])[w];
-      if (w == LWE_n) x += I.cst;
-      s_abar[w] = (uint16_t)((x + (1u << 20)) >> 21);
-    }
-    __syncthreads();
-    // acc = (0, X^(-bbar) * mu * (1 + X + ... + X^1023)): waves 0, 1 write A (halves), 2, 3 write B.
-    const uint32_t bbar = __builtin_amdgcn_readfirstlane(s_abar[LWE_n]);
+  const int rot_i = wave / 3, j = wave % 3;
+  const uint32_t idx = blockIdx.x * ROT + rot_i;
+  const bool active = idx < count;
+  const BrItem I = items[active ? idx : count - 1];  // an idle rotation repeats the last one and writes nothing
+  const int j1 = j == 2 ? 0 : j + 1, j2 = j == 0 ? 2 : j - 1;  // (j + 1) mod 3, (j + 2) mod 3
+  double(*X)[REGION] = s_x[rot_i];
+  // Regions: wavefront j's first (and, ROOMY, second) outgoing partial sums;
+  // the region that only this wavefront reads last is its inverse exchange.
+  double* mine = X[j];
+  double* mine2 = X[3 + j];
+  const double* in1 = X[j2];
+  const double* in2 = X[3 + j1];
+  double* inv = X[3 + j1];
+  double* lo_words = X[3];  // wavefront 2's inverse region
+  // Each accumulator polynomial p is held as the window p, -p, p: coefficient
+  // t of X^ab p is word (-ab mod 2048) + t.
+  const uint32_t* acc = s_acc[rot_i][c] + l;  // this lane's column of its half's polynomial
+  const double2* tw = &s_tw[0][lane];
+  double* xw = mine + c * XPOLY + l;
+  double* xr = mine + XROW * rho + ((lane >> 5) << 1) + ((lane >> 4) & 1);
+  if (j < 2) {
+    const uint32_t bbar = __builtin_amdgcn_readfirstlane(abar_of(I, LWE_n));
     const uint32_t rot = (2048u - bbar) & 2047u;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const uint32_t j = ((wave & 1) * 8 + r) * 64 + lane;
-      const bool neg = (j < (rot & 1023u)) != (rot >= 1024u);
-      acc[(wave >> 1) * RING_N + j] = (wave >> 1) == 0 ? 0u : (neg ? (0u - I.mu) : I.mu);
+    for (int R = 0; R < 16; ++R) {  // wavefront j: polynomial j
+      const uint32_t jj = 64 * R + lane;
+      const bool neg = (jj < (rot & 1023u)) != (rot >= 1024u);
+      const uint32_t v = j == 0 ? 0u : (neg ? (0u - I.mu) : I.mu);
+      uint32_t* p = s_acc[rot_i][j] + jj;
+      p[0] = p[2 * RING_N] = v;
+      p[RING_N] = 0u - v;
+    }
+  }
+  // Offset of digit j: rounding and the halves of the digits below it; the
+  // digit itself is then a signed 7-bit field.
+  const unsigned shift = 32 - BG_BIT * (j + 1);
+  const uint32_t offset = (1u << 10) + (j < 2 ? 1u << 17 : 0u) + (j < 1 ? 1u << 24 : 0u);
+  const double magic = 6755399441055744.0;  // 1.5 * 2^52: the sum's low words are the nearest integer
+  uint32_t abars = 0;
+  const __amdgpu_buffer_rsrc_t key =
+      __builtin_amdgcn_make_buffer_rsrc((void*)I.bk, 0, (int)BK_FFT_BYTES, 0x00027000);
+  const int lane16 = lane * 16;
+  int off = j * 6 * 8192;  // key batches of step i: ((3 i + j) * 2 + c) * 3 + channel
+  // The step's six batches in the order they are used, RING of them in flight.
+  const int order[6] = {j1 * 8192, (3 + j1) * 8192, j2 * 8192, (3 + j2) * 8192, j * 8192, (3 + j) * 8192};
+  double2 v[RING][8];
+#pragma unroll
+  for (int n = 0; n < RING; ++n)
+#pragma unroll
+    for (int m = 0; m < 8; ++m) key_load(v[n], key, lane16, off + order[n], m);
+  __syncthreads();
+  for (int i = 0; i < LWE_n; ++i, off += 18 * 8192) {
+    if ((i & 63) == 0) abars = i + lane < LWE_n ? abar_of(I, i + lane) : 0u;
+    const uint32_t ab = __builtin_amdgcn_readlane(abars, i & 63);
+    Cplx z[16];
+    {
+      const uint32_t* src = acc + ((0u - ab) & (2 * RING_N - 1));
+      uint32_t w[32], own[32];
+#pragma unroll
+      for (int R = 0; R < 32; ++R) w[R] = src[32 * R];
+#pragma unroll
+      for (int R = 0; R < 32; ++R) own[R] = acc[32 * R];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int R = 0; R < 32; ++R) {
+        const uint32_t D = (w[R] - own[R]) + offset;
+        const double d = (double)(int)__builtin_amdgcn_sbfe(D, shift, (unsigned)BG_BIT);
+        (R < 16 ? z[R & 15].r : z[R & 15].i) = d;
+      }
+    }
+    fwd_stage1<0>(z);
+    fwd_stage1<1>(z);
+    fwd_stage1<2>(z);
+    fwd_stage1<3>(z);
+    Cplx a[8], b[8];
+    wave_lds_sync();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) xw[XROW * q] = z[q].r;
+    wave_lds_sync();
+#pragma unroll
+    for (int m = 0; m < 8; ++m) a[m].r = xr[4 * m];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) b[m].r = xr[XPOLY + 4 * m];
+    wave_lds_sync();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) xw[XROW * q] = z[q].i;
+    wave_lds_sync();
+    const TwA ta = load_twa(tw);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) a[m].i = xr[4 * m];
+    const TwB tb = load_twb(tw);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) b[m].i = xr[XPOLY + 4 * m];
+    __builtin_amdgcn_sched_barrier(0);
+    fwd_stages456(a, ta);
+    swap_23(a);
+    fwd_stages78(a, tb);
+    __builtin_amdgcn_sched_barrier(0);
+    // s = a K_a + b K_b per channel: the channels the other wavefronts own
+    // first, then this one's.
+    Cplx s[8];
+    const int next = i + 1 < LWE_n ? off + 18 * 8192 : off;  // the next step's batches
+    auto mul = [&](const Cplx (&x)[8], auto n_t) {
+      constexpr int n = decltype(n_t)::value;
+      double2(&w)[8] = v[n % RING];
+      const int to = n + RING < 6 ? off + order[(n + RING) % 6] : next + order[(n + RING) % 6];
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        if constexpr (n % 2 == 0) {
+          s[m].r = x[m].r * w[m].x;
+          s[m].i = x[m].r * w[m].y;
+        } else {
+          s[m].r = __builtin_fma(x[m].r, w[m].x, s[m].r);
+          s[m].i = __builtin_fma(x[m].r, w[m].y, s[m].i);
+        }
+        s[m].r = __builtin_fma(-x[m].i, w[m].y, s[m].r);
+        s[m].i = __builtin_fma(x[m].i, w[m].x, s[m].i);
+        key_load(w, key, lane16, to, m);
+        if (m & 1) __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    auto put = [&](double* to) {
+      wave_lds_sync();
+#pragma unroll
+      for (int m = 0; m < 8; ++m) reinterpret_cast<double2*>(to)[m * 64 + lane] = make_double2(s[m].r, s[m].i);
+      wave_lds_sync();
+    };
+    mul(a, std::integral_constant<int, 0>());
+    fwd_stages456(b, ta);
+    swap_23(b);
+    fwd_stages78(b, tb);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(b, std::integral_constant<int, 1>());
+    put(mine);
+    mul(a, std::integral_constant<int, 2>());
+    mul(b, std::integral_constant<int, 3>());
+    put(mine2);
+    mul(a, std::integral_constant<int, 4>());
+    mul(b, std::integral_constant<int, 5>());
+    __syncthreads();
+    double2 r1[8], r2[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) r2[m] = reinterpret_cast<const double2*>(in2)[m * 64 + lane];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) r1[m] = reinterpret_cast<const double2*>(in1)[m * 64 + lane];
+    const TwB tbi = load_twb(tw);
+    const TwA tai = load_twa(tw);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      s[m].r += r1[m].x + r2[m].x;
+      s[m].i += r1[m].y + r2[m].y;
+    }
+    inv_stages87(s, tbi);
+    swap_23(s);
+    inv_stages654(s, tai);
+    double* iw = inv + XROW * rho + ((lane >> 5) << 1) + ((lane >> 4) & 1);
+    const double* ir = inv + XROW * 8 * c + l;
+    wave_lds_sync();
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      iw[4 * m] = s[m].r;
+      iw[XPOLY + 4 * m] = s[m].i;
+    }
+    wave_lds_sync();
+    const TwC tc = load_twc(tw);
+    Cplx h[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      h[m].r = ir[XROW * m];
+      h[m].i = ir[XPOLY + XROW * m];
+    }
+    wave_lds_sync();
+    __builtin_amdgcn_sched_barrier(0);
+    inv_stages3210(h, tc);
+    // Register m = (i8 i6 i5), lane (i7 | l): coefficient 32 R + l with
+    // R = 8 i8 + 4 i7 + 2 i6 + i5 (real part) and R + 16 (imaginary part).
+    uint32_t* ap = s_acc[rot_i][j & 1] + 128 * c + l;
+    uint32_t* lo_at = reinterpret_cast<uint32_t*>(lo_words) + 128 * c + l;
+    uint32_t old[16], hi[16];
+    if (j == 2) {
+      constexpr double half = (double)(1 << (LO_SHIFT - 1));
+#pragma unroll
+      for (int t = 0; t < 16; ++t) {
+        const int m = t & 7, R = 8 * (m >> 2) + 2 * ((m >> 1) & 1) + (m & 1) + 16 * (t >> 3);
+        const double x = t < 8 ? h[m].r : h[m].i;
+        const uint32_t wa = (uint32_t)__builtin_bit_cast(uint64_t, x + magic);
+        const uint64_t wb = __builtin_bit_cast(uint64_t, x + (magic + half));
+        lo_at[32 * R] = __builtin_amdgcn_sbfe(wa, 0u, (unsigned)LO_SHIFT);
+        lo_at[1024 + 32 * R] = __builtin_amdgcn_sbfe(
+            __builtin_amdgcn_alignbit((uint32_t)(wb >> 32), (uint32_t)wb, LO_SHIFT), 0u, (unsigned)LO_SHIFT);
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < 16; ++t) {
+        const int m = t & 7, R = 8 * (m >> 2) + 2 * ((m >> 1) & 1) + (m & 1) + 16 * (t >> 3);
+        old[t] = ap[32 * R];
+        uint32_t x = (uint32_t)__builtin_bit_cast(uint64_t, (t < 8 ? h[m].r : h[m].i) + magic);
+        uint32_t h5 = (x << 2) + x;
+        asm("" : "+v"(h5));
+        hi[t] = old[t] + (h5 << 2);
+      }
     }
     __syncthreads();
-    switch (wave) {
-      case 0: br4_rotate<0, 0>(I, acc, s_abar, s_buf[0], s_buf[1], s_x[0], s_x[2], s_tw[0], lane); break;
-      case 1: br4_rotate<1, 0>(I, acc, s_abar, s_buf[1], s_buf[0], s_x[1], s_x[3], s_tw[1], lane); break;
-      case 2: br4_rotate<0, 1>(I, acc, s_abar, s_buf[2], s_buf[3], s_x[2], s_x[0], s_tw[0], lane); break;
-      default: br4_rotate<1, 1>(I, acc, s_abar, s_buf[3], s_buf[2], s_x[3], s_x[1], s_tw[1], lane); break;
+    if (j < 2) {
+      uint32_t lo[16];
+#pragma unroll
+      for (int t = 0; t < 16; ++t) {
+        const int m = t & 7, R = 8 * (m >> 2) + 2 * ((m >> 1) & 1) + (m & 1) + 16 * (t >> 3);
+        lo[t] = lo_at[1024 * j + 32 * R];
+      }
+#pragma unroll
+      for (int t = 0; t < 16; ++t) {
+        const int m = t & 7, R = 8 * (m >> 2) + 2 * ((m >> 1) & 1) + (m & 1) + 16 * (t >> 3);
+        const uint32_t x = hi[t] + lo[t];
+        ap[32 * R] = ap[2 * RING_N + 32 * R] = x;
+        ap[RING_N + 32 * R] = 0u - x;
+      }
     }
-    for (int j = threadIdx.x; j < RING_N; j += 256) {
-      const uint32_t a = acc[j];
-      if (j == 0) I.out[0] = a;
-      else I.out[RING_N - j] = 0u - a;
-    }
-    if (threadIdx.x == 0) I.out[RING_N] = acc[RING_N];
+    __syncthreads();
+  }
+  // SampleExtract: a'_0 = A_0, a'_j = -A_(N-j), b' = B_0.
+  if (active) {
+    const uint32_t *A = s_acc[rot_i][0] + RING_N;  // -A
+    for (int jj = (int)threadIdx.x - rot_i * 192; jj < RING_N; jj += 192)
+      I.out[jj] = jj == 0 ? A[-RING_N] : A[RING_N - jj];
+    if (j == 0 && lane == 0) I.out[RING_N] = s_acc[rot_i][1][0];
   }
 }
 
@@ -599,7 +704,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
 // range of coefficients, whose partial results are added atomically into
 // outputs zeroed first when there is more than one range.
 // ---------------------------------------------------------------------------
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
 // Digit bytes of count gates (input a' = u1 + u2):
@@ -719,7 +823,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4 / RT))) v
 // Helpers
 // ---------------------------------------------------------------------------
 __global__ void make_br_items_kernel(BrItem* items, uint32_t count, const uint32_t* a, const uint32_t* b, int32_t ca,
-                                     int32_t cb, uint32_t cst, uint32_t mu, uint32_t* out, const uint32_t* bk) {
+                                     int32_t cb, uint32_t cst, uint32_t mu, uint32_t* out, const void* bk) {
   const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= count) return;
   BrItem it;
@@ -861,13 +965,9 @@ int noalloc_scratch_address(void** p) {
 // ---------------------------------------------------------------------------
 static inline hipStream_t S(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
-int launch_bk_transform(const uint32_t* bk_coeff, uint32_t* bk_ntt, const uint4* tw_fwd, void* stream) {
-  const uint32_t n_polys = LWE_n * 2 * ELL * 2;
-  uint32_t sc[4];
-  key_scale(sc);
-  const uint4 scale = make_uint4(sc[0], sc[1], sc[2], sc[3]);
-  hipLaunchKernelGGL(bk_transform_kernel<4>, dim3((n_polys + 3) / 4), dim3(256), 0, S(stream), bk_coeff, bk_ntt, tw_fwd,
-                     n_polys, scale);
+int launch_bk_transform(const uint32_t* bk_coeff, void* bk_fft, const FftTables* tables, void* stream) {
+  hipLaunchKernelGGL(bk_transform_kernel, dim3(LWE_n * 2 * ELL * FFT_CHANNELS), dim3(256), 0, S(stream), bk_coeff,
+                     reinterpret_cast<double2*>(bk_fft), reinterpret_cast<const double4*>(tables->dd));
   return (int)hipGetLastError();
 }
 
@@ -876,39 +976,20 @@ int launch_ksk_relayout(const uint32_t* ksk_in, uint32_t* ksk_out, void* stream)
   return (int)hipGetLastError();
 }
 
-int launch_br(const BrItem* items, uint32_t count, const uint4* tw_fwd, uint32_t waves_per_block, uint32_t blocks,
+int launch_br(const BrItem* items, uint32_t count, const FftTables* tables, uint32_t waves, uint32_t rot_per_block,
               void* stream) {
   if (count == 0) return 0;
-  const uint32_t need = (count + waves_per_block - 1) / waves_per_block;
-  if (blocks == 0 || blocks > need) blocks = need;
-  switch (waves_per_block) {
-    case 1: hipLaunchKernelGGL(br_kernel<1>, dim3(blocks), dim3(64), 0, S(stream), items, count, tw_fwd); break;
-    case 2: hipLaunchKernelGGL(br_kernel<2>, dim3(blocks), dim3(128), 0, S(stream), items, count, tw_fwd); break;
-    case 4: hipLaunchKernelGGL(br_kernel<4>, dim3(blocks), dim3(256), 0, S(stream), items, count, tw_fwd); break;
-    case 8: hipLaunchKernelGGL(br_kernel<8>, dim3(blocks), dim3(512), 0, S(stream), items, count, tw_fwd); break;
+  const dim3 grid((count + rot_per_block - 1) / rot_per_block), block(64 * waves * rot_per_block);
+  const double2* tw = reinterpret_cast<const double2*>(tables->lane);
+  switch (waves * 16 + rot_per_block) {
+    case 16 + 1: hipLaunchKernelGGL(br1_kernel<1>, grid, block, 0, S(stream), items, count, tw); break;
+    case 16 + 2: hipLaunchKernelGGL(br1_kernel<2>, grid, block, 0, S(stream), items, count, tw); break;
+    case 16 + 4: hipLaunchKernelGGL(br1_kernel<4>, grid, block, 0, S(stream), items, count, tw); break;
+    case 16 + 8: hipLaunchKernelGGL(br1_kernel<8>, grid, block, 0, S(stream), items, count, tw); break;
+    case 48 + 1: hipLaunchKernelGGL((br3_kernel<1, 3>), grid, block, 0, S(stream), items, count, tw); break;
+    case 48 + 2: hipLaunchKernelGGL((br3_kernel<2, 1>), grid, block, 0, S(stream), items, count, tw); break;
     default: return (int)hipErrorInvalidValue;
   }
-  return (int)hipGetLastError();
-}
-
-int launch_br2(const BrItem* items, uint32_t count, const uint4* tw_fwd, uint32_t rot_per_block, uint32_t blocks,
-               void* stream) {
-  if (count == 0) return 0;
-  const uint32_t need = (count + rot_per_block - 1) / rot_per_block;
-  if (blocks == 0 || blocks > need) blocks = need;
-  switch (rot_per_block) {
-    case 1: hipLaunchKernelGGL(br2_kernel<1>, dim3(blocks), dim3(128), 0, S(stream), items, count, tw_fwd); break;
-    case 2: hipLaunchKernelGGL(br2_kernel<2>, dim3(blocks), dim3(256), 0, S(stream), items, count, tw_fwd); break;
-    case 4: hipLaunchKernelGGL(br2_kernel<4>, dim3(blocks), dim3(512), 0, S(stream), items, count, tw_fwd); break;
-    default: return (int)hipErrorInvalidValue;
-  }
-  return (int)hipGetLastError();
-}
-
-int launch_br4(const BrItem* items, uint32_t count, const uint4* tw_fwd, uint32_t blocks, void* stream) {
-  if (count == 0) return 0;
-  if (blocks == 0 || blocks > count) blocks = count;
-  hipLaunchKernelGGL(br4_kernel, dim3(blocks), dim3(256), 0, S(stream), items, count, tw_fwd);
   return (int)hipGetLastError();
 }
 
@@ -957,7 +1038,7 @@ int launch_ks_group(const KsItem* items, uint32_t count, const uint32_t* ksk, ui
 }
 
 int launch_make_br_items(BrItem* items, uint32_t count, const uint32_t* a, const uint32_t* b, int32_t ca, int32_t cb,
-                         uint32_t cst, uint32_t mu, uint32_t* out, const uint32_t* bk, void* stream) {
+                         uint32_t cst, uint32_t mu, uint32_t* out, const void* bk, void* stream) {
   if (count == 0) return 0;
   hipLaunchKernelGGL(make_br_items_kernel, dim3((count + 255) / 256), dim3(256), 0, S(stream), items, count, a, b, ca,
                      cb, cst, mu, out, bk);

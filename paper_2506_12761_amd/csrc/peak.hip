@@ -5,19 +5,49 @@
 // each) and 12 N pointwise key products (Section 2.2: the external product
 // of a CMux, computed with negacyclic transforms); each is carried out as one
 // residue butterfly per prime of the two-prime residue system.  The bound
-// such a count is priced against can be derived from the instruction set
-// (lanes x clock divided by the VALU instructions of one multiplication) or
-// measured: this file measures it, with the very residue butterflies the
-// transforms execute (wave_ntt.h: lazy signed Cooley-Tukey forward,
-// Gentleman-Sande inverse, Shoup products), on register-resident values,
-// every CU busy and no memory traffic inside the loop.
+// such a count is priced against on the integer units can be derived from the
+// instruction set (lanes x clock divided by the VALU instructions of one
+// multiplication) or measured: this file measures it, with the residue
+// butterflies of the cheapest exact integer form (26-bit primes; lazy signed
+// Cooley-Tukey forward, Gentleman-Sande inverse, Shoup products), on
+// register-resident values, every CU busy and no memory traffic inside the
+// loop.  The blind rotation itself uses double-precision transforms (fft.h),
+// which need fewer instructions.
 #include <hip/hip_runtime.h>
 
 #include "vlp.h"
-#include "wave_ntt.h"
 
 namespace vlp {
 namespace {
+
+constexpr uint32_t PEAK_PRIME = 67104769u;  // 32766 * 2^11 + 1 < 2^26
+
+// y w mod p in (-p/2, 3p/2) for |y| < 2^31, a signed twiddle |w| < p/2 and
+// wq = floor(w 2^32 / p).
+__device__ __forceinline__ uint32_t shoup_s(uint32_t y, uint32_t w, uint32_t wq, uint32_t p) {
+  const uint32_t q = (uint32_t)__mulhi((int)y, (int)wq);
+  return w * y - q * p;
+}
+// Cooley-Tukey: (x, y) -> (x + w y, x - w y), never reduced.
+__device__ __forceinline__ void bfly_ct(uint32_t& x, uint32_t& y, uint32_t w, uint32_t wq, uint32_t p) {
+  const uint32_t u = x;
+  const uint32_t t = shoup_s(y, w, wq, p);
+  x = u + t;
+  y = u - t;
+}
+// Gentleman-Sande with a negated twiddle: (x, y) -> (x + y, (y - x) w); RED
+// reduces the sum (a Shoup product by 1).
+template <bool RED>
+__device__ __forceinline__ void bfly_gs_neg(uint32_t& x, uint32_t& y, uint32_t w, uint32_t wq, uint32_t p) {
+  const uint32_t u = x, v = y;
+  x = RED ? shoup_s(u + v, 1u, (uint32_t)((1ull << 32) / p), p) : u + v;
+  y = shoup_s(v - u, w, wq, p);
+}
+// Register of butterfly k of a stage that pairs register r with r | 2^RB.
+template <int RB>
+__device__ __forceinline__ constexpr int bfly_reg(int k) {
+  return ((k >> RB) << (RB + 1)) | (k & ((1 << RB) - 1));
+}
 
 constexpr int PEAK_THREADS = 256;
 constexpr int PEAK_WAVES_PER_CU = 32;  // 8 per SIMD: enough to hide the multiply latency
@@ -28,7 +58,7 @@ constexpr int BFLY_PER_ITER = 4 * 8;   // four stages (register strides 8, 4, 2,
 // transform runs inside a lane.
 template <bool INV>
 __global__ __launch_bounds__(PEAK_THREADS) void butterfly_peak_kernel(uint32_t* out, uint32_t seed, int iters) {
-  constexpr uint32_t p = Prime<0>::P;
+  constexpr uint32_t p = PEAK_PRIME;
   const uint32_t tid = blockIdx.x * PEAK_THREADS + threadIdx.x;
   uint32_t x[16], w[8], wp[8];
 #pragma unroll
@@ -53,22 +83,22 @@ __global__ __launch_bounds__(PEAK_THREADS) void butterfly_peak_kernel(uint32_t* 
 #pragma unroll
     for (int k = 0; k < 8; ++k) {  // register stride 8
       const int r = bfly_reg<3>(k);
-      if (INV) bfly_gs_neg<2, false>(x[r], x[r | 8], w[k], wp[k], p); else bfly_ct(x[r], x[r | 8], w[k], wp[k], p);
+      if (INV) bfly_gs_neg<false>(x[r], x[r | 8], w[k], wp[k], p); else bfly_ct(x[r], x[r | 8], w[k], wp[k], p);
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) {  // stride 4
       const int r = bfly_reg<2>(k);
-      if (INV) bfly_gs_neg<4, false>(x[r], x[r | 4], w[k], wp[k], p); else bfly_ct(x[r], x[r | 4], w[k], wp[k], p);
+      if (INV) bfly_gs_neg<false>(x[r], x[r | 4], w[k], wp[k], p); else bfly_ct(x[r], x[r | 4], w[k], wp[k], p);
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) {  // stride 2
       const int r = bfly_reg<1>(k);
-      if (INV) bfly_gs_neg<8, false>(x[r], x[r | 2], w[k], wp[k], p); else bfly_ct(x[r], x[r | 2], w[k], wp[k], p);
+      if (INV) bfly_gs_neg<false>(x[r], x[r | 2], w[k], wp[k], p); else bfly_ct(x[r], x[r | 2], w[k], wp[k], p);
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) {  // stride 1
       const int r = bfly_reg<0>(k);
-      if (INV) bfly_gs_neg<16, true>(x[r], x[r | 1], w[k], wp[k], p); else bfly_ct(x[r], x[r | 1], w[k], wp[k], p);
+      if (INV) bfly_gs_neg<true>(x[r], x[r | 1], w[k], wp[k], p); else bfly_ct(x[r], x[r | 1], w[k], wp[k], p);
     }
   }
   uint32_t s = 0;

@@ -23,7 +23,7 @@ struct vlp_ctx {
   bool own_stream = false;
   size_t budget = 0, used = 0;
   std::string err;
-  uint4* tw_fwd = nullptr;  // device twiddle table
+  FftTables* tables = nullptr;  // device twiddle tables
   int num_cus = 256;
   vlp_tuning tune{4, 1, 512, 0};
   // Grow-only scratch for the elementwise calls.
@@ -46,7 +46,7 @@ struct vlp_ctx {
 
 struct vlp_keyset {
   vlp_ctx* ctx;
-  uint32_t* bk_ntt;
+  void* bk;  // transformed bootstrapping key
   uint32_t* ksk;
   int users;  // live programs made with it
 };
@@ -178,36 +178,40 @@ bool ranges_overlap(const void* a, size_t an, const void* b, size_t bn) {
 int mark_begin(vlp_ctx* ctx);
 void mark_end(vlp_ctx* ctx, int id, int kind, uint64_t items);
 
-// Blind rotations are launched in rounds that the device holds at once
-// (CUs x workgroups per CU x rotations per workgroup): rotations that start
-// together walk the key in step, so each key row reaches L2 once for many of
-// them (a persistent loop over many rounds let them drift apart and re-fetch
-// the key: up to ~36 MB instead of ~0.5 MB of key traffic per rotation).
-// Automatic mode: a round of at most 2 rotations per CU runs on the
-// four-wavefront kernel (half the latency), larger rounds on the
-// two-wavefront kernel.
+// Blind rotations are launched in rounds that the device holds at once:
+// rotations that start together walk the key in step, so each key row reaches
+// L2 once for many of them (a persistent loop over many rounds let them drift
+// apart and re-fetch it).
+// Automatic mode picks each round by what is left, in rotations per CU, from
+// the measured times of a round: up to 1 per CU 3.3 ms (three wavefronts, one
+// rotation per workgroup), up to 2 4.5 ms (three wavefronts, two), up to 4
+// 7.5 ms (one wavefront each, one per SIMD), up to 8 12.0 ms (two per SIMD).
+// So the smallest round that holds the rest, except that 4 to 5 per CU run as
+// 4 and 1 (10.8 ms); splitting the others gains nothing (3 as 2 and 1: 7.8 ms;
+// 6 as 4 and 2: 12.0 ms).
+struct BrRound {
+  uint32_t waves, rot_per_block, rotations;
+};
+BrRound next_round(const vlp_tuning& t, uint32_t cus, uint32_t left) {
+  const uint32_t rpb = t.br_rotations_per_block, bpc = t.br_blocks_per_cu;
+  switch (t.br_waves_per_rotation) {
+    case 1: return {1, rpb, cus * bpc * rpb};
+    case 2: return {3, std::min(rpb, 2u), cus * bpc * rpb};
+    case 4: return {3, 1, cus * bpc};
+    default: break;
+  }
+  if (left <= cus) return {3, 1, cus};
+  if (left <= 2 * cus) return {3, 2, 2 * cus};
+  if (left <= 5 * cus) return {1, 4, 4 * cus};
+  return {1, 8, 8 * cus};
+}
+
 int timed_br(vlp_ctx* ctx, const BrItem* items, uint32_t count) {
-  const uint32_t mode = ctx->tune.br_waves_per_rotation, bpc = ctx->tune.br_blocks_per_cu;
-  const uint32_t rpb = ctx->tune.br_rotations_per_block, cus = (uint32_t)ctx->num_cus;
-  const uint32_t small = cus * 2;  // rotations one round of the four-wavefront kernel holds
   for (uint32_t first = 0; first < count;) {
-    const uint32_t rem = count - first;
-    uint32_t n;
-    int e;
+    const BrRound r = next_round(ctx->tune, (uint32_t)ctx->num_cus, count - first);
+    const uint32_t n = std::min(r.rotations, count - first);
     const int m = mark_begin(ctx);
-    if (mode == 4 || (mode == 0 && rem <= small)) {
-      const uint32_t blocks = mode == 4 ? cus * bpc : small;
-      n = std::min(blocks, rem);
-      e = launch_br4(items + first, n, ctx->tw_fwd, blocks, ctx->stream);
-    } else if (mode == 1) {
-      const uint32_t blocks = cus * bpc;
-      n = std::min(blocks * rpb, rem);
-      e = launch_br(items + first, n, ctx->tw_fwd, rpb, blocks, ctx->stream);
-    } else {
-      const uint32_t blocks = cus * bpc;
-      n = std::min(blocks * rpb, rem);
-      e = launch_br2(items + first, n, ctx->tw_fwd, rpb, blocks, ctx->stream);
-    }
+    const int e = launch_br(items + first, n, ctx->tables, r.waves, r.rot_per_block, ctx->stream);
     mark_end(ctx, m, 0, n);
     if (e != 0) return e;
     first += n;
@@ -277,7 +281,7 @@ uint32_t encode_bit(uint32_t bit) { return bit ? MU : 0u - MU; }
 // ---------------------------------------------------------------------------
 // Context
 // ---------------------------------------------------------------------------
-extern "C" const char* vlp_version(void) { return "vlp 0.3 (gfx950, two-prime NTT)"; }
+extern "C" const char* vlp_version(void) { return "vlp 0.4 (gfx950, exact double-precision transforms)"; }
 
 extern "C" void vlp_default_params(vlp_params* p) {
   if (!p) return;
@@ -337,16 +341,16 @@ extern "C" vlp_status vlp_ctx_create(vlp_ctx** out, const vlp_params* p, int dev
     delete ctx;
     return VLP_EHIP;
   }
-  std::vector<uint32_t> tf(4 * RING_N);
-  make_twiddles(tf.data());
-  vlp_status st = dev_alloc(ctx, (void**)&ctx->tw_fwd, RING_N * 16);
+  std::vector<FftTables> host(1);
+  make_fft_tables(host.data());
+  vlp_status st = dev_alloc(ctx, (void**)&ctx->tables, sizeof(FftTables));
   if (st == VLP_OK) {
-    e = hipMemcpy(ctx->tw_fwd, tf.data(), RING_N * 16, hipMemcpyHostToDevice);
-    if (e != hipSuccess) st = fail(ctx, VLP_EHIP, "twiddle upload: %s", hipGetErrorString(e));
+    e = hipMemcpy(ctx->tables, host.data(), sizeof(FftTables), hipMemcpyHostToDevice);
+    if (e != hipSuccess) st = fail(ctx, VLP_EHIP, "table upload: %s", hipGetErrorString(e));
   }
   if (st != VLP_OK) {
     g_create_err = ctx->err;
-    dev_free(ctx, ctx->tw_fwd, RING_N * 16);
+    dev_free(ctx, ctx->tables, sizeof(FftTables));
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;
     return st;
@@ -370,7 +374,7 @@ extern "C" vlp_status vlp_ctx_destroy(vlp_ctx* ctx) {
   }
   for (hipEvent_t e : ctx->event_pool) (void)hipEventDestroy(e);
   dev_free(ctx, ctx->scratch, ctx->scratch_bytes);
-  dev_free(ctx, ctx->tw_fwd, RING_N * 16);
+  dev_free(ctx, ctx->tables, sizeof(FftTables));
   if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
   delete ctx;
   return VLP_OK;
@@ -416,17 +420,17 @@ extern "C" vlp_status vlp_keyset_load(vlp_ctx* ctx, const uint32_t* bk_dev, cons
   if (!bk_dev || !ksk_dev || !out) return fail(ctx, VLP_EINVAL, "null argument");
   *out = nullptr;
   vlp_keyset* ks = new vlp_keyset{ctx, nullptr, nullptr, 0};
-  vlp_status st = dev_alloc(ctx, (void**)&ks->bk_ntt, BK_NTT_WORDS * 4);
+  vlp_status st = dev_alloc(ctx, (void**)&ks->bk, BK_FFT_BYTES);
   if (st == VLP_OK) st = dev_alloc(ctx, (void**)&ks->ksk, KSK_WORDS * 4);
   if (st != VLP_OK) {
-    dev_free(ctx, ks->bk_ntt, BK_NTT_WORDS * 4);
+    dev_free(ctx, ks->bk, BK_FFT_BYTES);
     delete ks;
     return st;
   }
-  int e = launch_bk_transform(bk_dev, ks->bk_ntt, ctx->tw_fwd, ctx->stream);
+  int e = launch_bk_transform(bk_dev, ks->bk, ctx->tables, ctx->stream);
   if (e == 0) e = launch_ksk_relayout(ksk_dev, ks->ksk, ctx->stream);
   if (e != 0) {
-    dev_free(ctx, ks->bk_ntt, BK_NTT_WORDS * 4);
+    dev_free(ctx, ks->bk, BK_FFT_BYTES);
     dev_free(ctx, ks->ksk, KSK_WORDS * 4);
     delete ks;
     return fail(ctx, VLP_EHIP, "key preparation launch: %s", hipGetErrorString((hipError_t)e));
@@ -451,7 +455,7 @@ extern "C" vlp_status vlp_keyset_destroy(vlp_keyset* ks) {
   }
   if (ks->users) return fail(ctx, VLP_EBUSY, "keyset still used by %d programs", ks->users);
   (void)hipStreamSynchronize(ctx->stream);
-  dev_free(ctx, ks->bk_ntt, BK_NTT_WORDS * 4);
+  dev_free(ctx, ks->bk, BK_FFT_BYTES);
   dev_free(ctx, ks->ksk, KSK_WORDS * 4);
   ctx->live_keysets--;
   delete ks;
@@ -471,7 +475,7 @@ extern "C" vlp_status vlp_bootstrap(vlp_ctx* ctx, const vlp_keyset* ks, const ui
   vlp_status st = ensure_scratch(ctx, B * sizeof(BrItem));
   if (st != VLP_OK) return st;
   BrItem* items = (BrItem*)ctx->scratch;
-  LAUNCHCHECK(ctx, launch_make_br_items(items, (uint32_t)B, in_dev, nullptr, 1, 0, 0, mu, out_dev, ks->bk_ntt, ctx->stream));
+  LAUNCHCHECK(ctx, launch_make_br_items(items, (uint32_t)B, in_dev, nullptr, 1, 0, 0, mu, out_dev, ks->bk, ctx->stream));
   LAUNCHCHECK(ctx, timed_br(ctx, items, (uint32_t)B));
   return VLP_OK;
 }
@@ -533,10 +537,10 @@ vlp_status gate_run(vlp_ctx* ctx, const vlp_keyset* ks, vlp_gate_op op, const ui
   int32_t ca, cb;
   uint32_t cst;
   gate_coeffs((uint8_t)op, &ca, &cb, &cst);
-  LAUNCHCHECK(ctx, launch_make_br_items(bri, (uint32_t)B, a_dev, b_dev, ca, cb, cst, MU, ext, ks->bk_ntt, ctx->stream));
+  LAUNCHCHECK(ctx, launch_make_br_items(bri, (uint32_t)B, a_dev, b_dev, ca, cb, cst, MU, ext, ks->bk, ctx->stream));
   if (op == VLP_MUX)
     LAUNCHCHECK(ctx, launch_make_br_items(bri + B, (uint32_t)B, a_dev, c_dev, -1, 1, 0u - MU, MU, ext + B * CT_N,
-                                          ks->bk_ntt, ctx->stream));
+                                          ks->bk, ctx->stream));
   const bool prof = ctx->prof;
   ctx->prof = prof && timed;
   int e = timed_br(ctx, bri, (uint32_t)units);
@@ -871,7 +875,7 @@ extern "C" vlp_status vlp_program_create_ex(vlp_ctx* ctx, const vlp_keyset* ks_c
     it.cst = cst;
     it.mu = MU;
     it.out = out;
-    it.bk = ks->bk_ntt;
+    it.bk = ks->bk;
     return it;
   };
   std::vector<const uint32_t*> hm;  // operand lists of k-input XOR items
@@ -900,7 +904,7 @@ extern "C" vlp_status vlp_program_create_ex(vlp_ctx* ctx, const vlp_keyset* ks_c
     it.cst = cst;
     it.mu = MU;
     it.out = out;
-    it.bk = ks->bk_ntt;
+    it.bk = ks->bk;
     return it;
   };
   std::vector<BrItem> hb;
