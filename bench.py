@@ -703,8 +703,8 @@ def main():
             traffic = TRAFFIC_MEASURED["bytes_per_launch"]
         roofline = br_roofline(prof)
         roofline.update({"traffic": traffic, "traffic_unit": "B per launch", "algorithmic_bytes_per_launch": alg_bytes,
-                         "kernel": {0: "br1_kernel (br3_kernel for short rounds)", 1: "br1_kernel", 2: "br3_kernel",
-                                    4: "br3_kernel"}[launch["br_waves_per_rotation"]]})
+                         "kernel": {0: "br1_kernel (br3_kernel, br6_kernel for short rounds)", 1: "br1_kernel",
+                                    2: "br3_kernel", 4: "br6_kernel"}[launch["br_waves_per_rotation"]]})
 
     config4 = None
     if not args.no_config4 and args.workload != "idm-65536":

@@ -261,13 +261,15 @@ vlp_status vlp_program_destroy(vlp_program *prog);
 /* ---- Tuning knobs of the batched kernels (picked by the autotuner).
  * br_waves_per_rotation : the blind-rotation kernel:
  *                          1 = one wavefront per rotation;
- *                          2, 4 = three wavefronts per rotation (one per
- *                              digit, then one per product channel): lower
- *                              latency, fewer rotations in flight; 4: one
- *                              rotation per workgroup;
+ *                          4 = six wavefronts per rotation (half the
+ *                              latency or less, one rotation per workgroup
+ *                              and CU at a time);
+ *                          2 = three wavefronts per rotation, two rotations
+ *                              per workgroup (one rotation per workgroup
+ *                              runs as 4);
  *                          0 = automatic (default): each round picks by the
- *                              rotations left (up to 2 per CU the second
- *                              kind, more the first, at most 8 per CU)
+ *                              rotations left: at most 1 per CU six, at most
+ *                              2 three, more one (at most 8 per CU)
  * br_rotations_per_block: rotations per workgroup (1 wavefront per rotation:
  *                          1, 2, 4, 8; br_waves_per_rotation = 2: 1, 2, 4,
  *                          of which at most 2 share a workgroup; 4: 1);

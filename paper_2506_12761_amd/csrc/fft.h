@@ -248,6 +248,21 @@ __device__ __forceinline__ void inv_stages3210(Cplx (&z)[8], const TwC& t) {
   for (int m = 0; m < 4; ++m) bf_inv<false>(z[m], z[m + 4], W_RE[0], W_IM[0]);
 }
 
+// Forward stages 1, 2, 3 in register (i7 i6 i5), lane (i8 | i4..i0).
+__device__ __forceinline__ void fwd_stages123(Cplx (&z)[8], const TwC& t) {
+#pragma unroll
+  for (int m = 0; m < 4; ++m) bf_fwd<false>(z[m], z[m + 4], t.t10.x, t.t10.y);
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    bf_fwd<false>(z[m], z[m + 2], t.t9.x, t.t9.y);
+    bf_fwd<true>(z[m + 4], z[m + 6], t.t9.x, t.t9.y);
+  }
+  bf_fwd<false>(z[0], z[1], t.t7.x, t.t7.y);
+  bf_fwd<true>(z[2], z[3], t.t7.x, t.t7.y);
+  bf_fwd<false>(z[4], z[5], t.t8.x, t.t8.y);
+  bf_fwd<true>(z[6], z[7], t.t8.x, t.t8.y);
+}
+
 // Exchange between layouts 1 and 2 through LDS, one component at a time:
 // element i of a polynomial is double 33 (i >> 5) + (i & 31): 64-bit accesses
 // are served 16 lanes at a time by 32 banks, so 16 consecutive doubles (layout

@@ -34,6 +34,21 @@ void make_fft_tables(FftTables* t) {
       t->lane[e][L][1] = (double)s;
     }
   }
+  // Half-size inverse (i8 = hf): stages 8, 7 in lane (i3 i2 | i4 | i7 i6 i5),
+  // 6, 5 in lane (i1 i0 | i4 | i7 i6 i5), 4, 3 in lane (i7 i6 | i3..i0), 2, 1 uniform.
+  for (int hf = 0; hf < 2; ++hf)
+    for (int L = 0; L < 64; ++L) {
+      const int i3 = L >> 5, i2 = (L >> 4) & 1, i4 = (L >> 3) & 1, top = (hf << 3) | (L & 7);  // i8 i7 i6 i5
+      const int b7 = (((top << 1) | i4) << 2) | (i3 << 1) | i2;                                // i8..i2
+      const int mid = (hf << 2) | (L >> 4);                                                    // i8 i7 i6
+      const int k_of[8] = {8, 7, 6, 5, 4, 3, 2, 1};
+      const int b_of[8] = {b7 << 1, b7, ((top << 1) | i4) << 1, (top << 1) | i4, mid << 1, mid, hf << 1, hf};
+      for (int e = 0; e < 8; ++e) {
+        stage_twiddle(k_of[e], b_of[e], &c, &s);
+        t->half[hf][e][L][0] = (double)c;
+        t->half[hf][e][L][1] = (double)s;
+      }
+    }
   for (int k = 0; k < 9; ++k)
     for (int b = 0; b < (1 << k); ++b) {
       stage_twiddle(k, b, &c, &s);

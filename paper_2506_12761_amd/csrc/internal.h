@@ -74,6 +74,7 @@ int noalloc_scratch_address(void** p);
 // index 2^k + block (the key's transform; entry 0 unused).
 struct FftTables {
   double lane[11][64][2];
+  double half[2][8][64][2];
   double dd[512][4];
 };
 void make_fft_tables(FftTables* t);
@@ -82,8 +83,8 @@ void make_fft_tables(FftTables* t);
 // HIP error of the launch.  `tables` is a device pointer.
 int launch_bk_transform(const uint32_t* bk_coeff, void* bk_fft, const FftTables* tables, void* stream);
 int launch_ksk_relayout(const uint32_t* ksk_in, uint32_t* ksk_out, void* stream);
-// Blind rotations by `waves` (1 or 3) wavefronts each, rot_per_block of them
-// per workgroup (1 wavefront: 1, 2, 4, 8; 3: 1, 2).
+// Blind rotations by `waves` (1, 3 or 6) wavefronts each, rot_per_block of
+// them per workgroup (1 wavefront: 1, 2, 4, 8; 3: 2; 6: 1).
 int launch_br(const BrItem* items, uint32_t count, const FftTables* tables, uint32_t waves, uint32_t rot_per_block,
               void* stream);
 // ServerEnc over a flat [count][631] array; out == pk runs in place.

@@ -123,10 +123,11 @@ __global__ void ksk_relayout_kernel(const uint32_t* __restrict__ in, uint32_t* _
 // kernel it replaces: 21.7 ms, 94k/s), 1,024 at 4 per CU in 7.5 ms (10.9 ms).
 // ---------------------------------------------------------------------------
 // The wavefronts of a workgroup read the same key: a barrier every few steps
-// keeps them close enough to share it in the L1 and L2.  Every step: 8.1 ms
-// for 1,024 rotations at 4 per CU; every 8: 7.5 ms; every 64: 12.4 ms for
-// 2,048 at 8 per CU instead of 12.0.
-constexpr int STEPS_PER_BARRIER = 8;
+// keeps them close enough to share it in the L1 and L2.  With 8 per CU every
+// step is best (2,048 rotations back to back: 12.20 ms; every 8 steps 12.38,
+// every 16 12.45); with 4, one per SIMD, the stalls of a barrier are not
+// filled by another wavefront (1,024: 7.86 ms; every 8 7.60, every 16 7.50).
+constexpr int steps_per_barrier(int rot) { return rot == 8 ? 1 : 16; }
 
 constexpr uint32_t DEC_OFFSET = (1u << 31) + (1u << 24) + (1u << 17) + (1u << 10);
 // Balanced digit l of D (with DEC_OFFSET added) is its 7-bit field minus 64,
@@ -162,6 +163,22 @@ __device__ __forceinline__ void key_load(double2 (&v)[8], __amdgpu_buffer_rsrc_t
   const v4i w = __builtin_amdgcn_raw_buffer_load_b128(key, lane16 + (m & 3) * 1024, off + (m >> 2) * 4096, 0);
   v[m] = __builtin_bit_cast(double2, w);
 }
+// Key rows are touched PREFETCH_STEPS ahead of their use, so that the loads of
+// the wavefronts find them in L2: each XCD has its own L2, and its workgroups
+// (blockIdx mod 8) share the step's 18 batches among their wavefronts (`batch`
+// counts an XCD's wavefronts, those past 18 touch nothing), one 128-byte line
+// per lane.  1,024 rotations with the key in HBM: 9.2 -> 7.7 ms (in the
+// last-level cache 7.6 ms either way); 2,048: 13.5 -> 12.9 ms.  The other
+// kernels hold the loads of a whole step or of its longest wait and gain
+// nothing (br6_kernel, 256: 3.05 -> 2.93 ms, but 2.77 -> 2.93 from the cache).
+constexpr int PREFETCH_STEPS = 4, NUM_XCD = 8, STEP_BATCHES = 2 * ELL * FFT_CHANNELS;
+__device__ __forceinline__ uint32_t key_touch(__amdgpu_buffer_rsrc_t key, int lane, int i, int batch) {
+  const int step = i + PREFETCH_STEPS;
+  const bool use = batch < STEP_BATCHES && step < LWE_n;  // else: offsets out of the buffer's range load nothing
+  return __builtin_amdgcn_raw_buffer_load_b32(key, lane * 128 + (use ? 0 : (int)BK_FFT_BYTES),
+                                              use ? (step * STEP_BATCHES + batch) * 8192 : 0, 0);
+}
+
 // s += a * v for one channel; NEXT: replaces v by the batch at offset off.
 template <bool NEXT>
 __device__ __forceinline__ void key_products(Cplx (&s)[8], const Cplx (&a)[8], double2 (&v)[8],
@@ -189,7 +206,7 @@ __global__ __launch_bounds__(64 * ROT) __attribute__((amdgpu_waves_per_eu(2))) v
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t idx = blockIdx.x * ROT + wave;
   if (idx >= count) {  // no rotation: only meets the others at their barriers
-    for (int i = 0; i < LWE_n; i += STEPS_PER_BARRIER) __builtin_amdgcn_s_barrier();
+    for (int i = 0; i < LWE_n; i += steps_per_barrier(ROT)) __builtin_amdgcn_s_barrier();
     return;
   }
   const BrItem I = items[idx];
@@ -214,6 +231,7 @@ __global__ __launch_bounds__(64 * ROT) __attribute__((amdgpu_waves_per_eu(2))) v
   const double magic_lo = magic + (c ? (double)(1 << (LO_SHIFT - 1)) : 0.0);
   uint32_t lo_shift = c ? LO_SHIFT : 0;
   asm("" : "+v"(lo_shift));  // one funnel shift by a register, not a shift and a select
+  const int unit = wave * (int)((gridDim.x + NUM_XCD - 1) / NUM_XCD) + (int)(blockIdx.x / NUM_XCD);
   uint32_t own[32];  // this lane's accumulator coefficients
 #pragma unroll
   for (int R = 0; R < 32; ++R) own[R] = acc[32 * R];
@@ -226,7 +244,7 @@ __global__ __launch_bounds__(64 * ROT) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
   for (int m = 0; m < 8; ++m) key_load(v, key, lane16, off, m);
   for (int i = 0; i < LWE_n; ++i) {
-    if (i % STEPS_PER_BARRIER == 0) __builtin_amdgcn_s_barrier();
+    if (i % steps_per_barrier(ROT) == 0) __builtin_amdgcn_s_barrier();
     if ((i & 63) == 0) abars = i + lane < LWE_n ? abar_of(I, i + lane) : 0u;
     const uint32_t ab = __builtin_amdgcn_readlane(abars, i & 63);
     const int abh = (int)(ab >> 5), abl = (int)(ab & 31);
@@ -331,6 +349,8 @@ __global__ __launch_bounds__(64 * ROT) __attribute__((amdgpu_waves_per_eu(2))) v
     digit(std::true_type(), 0);
 #pragma unroll 1
     for (int shift = 9; shift > 0; shift -= 7) digit(std::false_type(), (unsigned)shift);
+    const uint32_t touched = key_touch(key, lane, i, unit);
+    __builtin_amdgcn_sched_barrier(0);
     // Inverse transforms; each exchange's reads are in flight while the other
     // channels are worked on.
     TwB tb = load_twb(tw);
@@ -411,6 +431,7 @@ __global__ __launch_bounds__(64 * ROT) __attribute__((amdgpu_waves_per_eu(2))) v
       acc[32 * R] = own[R];
     }
     acc[-32] = 0u - own[31];
+    asm volatile("" ::"v"(touched));
   }
   wave_lds_sync();
   // SampleExtract: a'_0 = A_0, a'_j = -A_(N-j), b' = B_0.
@@ -426,33 +447,30 @@ __global__ __launch_bounds__(64 * ROT) __attribute__((amdgpu_waves_per_eu(2))) v
 }
 
 // ---------------------------------------------------------------------------
-// Blind rotation, three wavefronts per rotation (br3_kernel), for rounds of at
-// most two rotations per CU: wavefront j transforms digit j of both
-// accumulator halves, multiplies with its two key rows, hands the other
-// wavefronts their channels' partial sums through LDS and transforms channel j
-// (hi_A, hi_B, packed lo) back; the packed channel's integers go to the other
-// two through LDS.  Three barriers per step.  Bound: the latency of that
-// chain (about 1,300 VALU instructions, 6.8k of 11.7k clocks a step for a
-// rotation alone; the rest are LDS round trips and barriers).
-// One rotation per workgroup (RING = 3: registers for 24 key loads in
-// flight): 3.06 ms for one rotation, 3.3 ms for 256 (3.8 ms before, with four
-// wavefronts and two-prime transforms); RING = 1: 3.30 and 3.38.  Two per
-// workgroup share barriers and fill each other's gaps: 512 in 4.46 ms
-// (6.3 ms), 6.3 ms as two rounds of one.
+// Blind rotation, three wavefronts per rotation and two rotations per
+// workgroup (br3_kernel), for rounds of one to two rotations per CU: wavefront
+// j transforms digit j of both accumulator halves, multiplies with its two key
+// rows, hands the other wavefronts their channels' partial sums through LDS
+// and transforms channel j (hi_A, hi_B, packed lo) back; the packed channel's
+// integers go to the other two through LDS.  Three barriers per step.  Bound:
+// the latency of that chain (about 1,300 VALU instructions, LDS round trips
+// and barriers), which the two rotations fill for each other: 512 rotations in
+// 4.4 ms (6.3 ms before, with four wavefronts and two-prime transforms), one
+// per workgroup 3.1 ms for 256.
 // ---------------------------------------------------------------------------
-template <int ROT, int RING>
-__global__ __launch_bounds__(192 * ROT) __attribute__((amdgpu_waves_per_eu(2))) void br3_kernel(
+constexpr int BR3_ROT = 2;
+__global__ __launch_bounds__(192 * BR3_ROT) __attribute__((amdgpu_waves_per_eu(2))) void br3_kernel(
     const BrItem* __restrict__ items, uint32_t count, const double2* __restrict__ lane_tw) {
   constexpr int REGION = 2 * XPOLY;  // doubles: one polynomial's values (1,024 doubles), padded for the exchange
   constexpr int REGIONS = 6;
-  __shared__ double s_x[ROT][REGIONS][REGION];
+  __shared__ double s_x[BR3_ROT][REGIONS][REGION];
   __shared__ double2 s_tw[LANE_TW][64];
-  __shared__ uint32_t s_acc[ROT][2][3 * RING_N];
-  for (int e = threadIdx.x; e < LANE_TW * 64; e += 192 * ROT) s_tw[0][e] = lane_tw[e];
+  __shared__ uint32_t s_acc[BR3_ROT][2][3 * RING_N];
+  for (int e = threadIdx.x; e < LANE_TW * 64; e += 192 * BR3_ROT) s_tw[0][e] = lane_tw[e];
   const int lane = threadIdx.x & 63, c = lane >> 5, l = lane & 31, rho = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int rot_i = wave / 3, j = wave % 3;
-  const uint32_t idx = blockIdx.x * ROT + rot_i;
+  const uint32_t idx = blockIdx.x * BR3_ROT + rot_i;
   const bool active = idx < count;
   const BrItem I = items[active ? idx : count - 1];  // an idle rotation repeats the last one and writes nothing
   const int j1 = j == 2 ? 0 : j + 1, j2 = j == 0 ? 2 : j - 1;  // (j + 1) mod 3, (j + 2) mod 3
@@ -494,13 +512,11 @@ __global__ __launch_bounds__(192 * ROT) __attribute__((amdgpu_waves_per_eu(2))) 
       __builtin_amdgcn_make_buffer_rsrc((void*)I.bk, 0, (int)BK_FFT_BYTES, 0x00027000);
   const int lane16 = lane * 16;
   int off = j * 6 * 8192;  // key batches of step i: ((3 i + j) * 2 + c) * 3 + channel
-  // The step's six batches in the order they are used, RING of them in flight.
+  // The step's six batches in the order they are used; v holds the next one.
   const int order[6] = {j1 * 8192, (3 + j1) * 8192, j2 * 8192, (3 + j2) * 8192, j * 8192, (3 + j) * 8192};
-  double2 v[RING][8];
+  double2 v[8];
 #pragma unroll
-  for (int n = 0; n < RING; ++n)
-#pragma unroll
-    for (int m = 0; m < 8; ++m) key_load(v[n], key, lane16, off + order[n], m);
+  for (int m = 0; m < 8; ++m) key_load(v, key, lane16, off + order[0], m);
   __syncthreads();
   for (int i = 0; i < LWE_n; ++i, off += 18 * 8192) {
     if ((i & 63) == 0) abars = i + lane < LWE_n ? abar_of(I, i + lane) : 0u;
@@ -556,20 +572,19 @@ __global__ __launch_bounds__(192 * ROT) __attribute__((amdgpu_waves_per_eu(2))) 
     const int next = i + 1 < LWE_n ? off + 18 * 8192 : off;  // the next step's batches
     auto mul = [&](const Cplx (&x)[8], auto n_t) {
       constexpr int n = decltype(n_t)::value;
-      double2(&w)[8] = v[n % RING];
-      const int to = n + RING < 6 ? off + order[(n + RING) % 6] : next + order[(n + RING) % 6];
+      const int to = n < 5 ? off + order[n + 1] : next + order[0];
 #pragma unroll
       for (int m = 0; m < 8; ++m) {
         if constexpr (n % 2 == 0) {
-          s[m].r = x[m].r * w[m].x;
-          s[m].i = x[m].r * w[m].y;
+          s[m].r = x[m].r * v[m].x;
+          s[m].i = x[m].r * v[m].y;
         } else {
-          s[m].r = __builtin_fma(x[m].r, w[m].x, s[m].r);
-          s[m].i = __builtin_fma(x[m].r, w[m].y, s[m].i);
+          s[m].r = __builtin_fma(x[m].r, v[m].x, s[m].r);
+          s[m].i = __builtin_fma(x[m].r, v[m].y, s[m].i);
         }
-        s[m].r = __builtin_fma(-x[m].i, w[m].y, s[m].r);
-        s[m].i = __builtin_fma(x[m].i, w[m].x, s[m].i);
-        key_load(w, key, lane16, to, m);
+        s[m].r = __builtin_fma(-x[m].i, v[m].y, s[m].r);
+        s[m].i = __builtin_fma(x[m].i, v[m].x, s[m].i);
+        key_load(v, key, lane16, to, m);
         if (m & 1) __builtin_amdgcn_sched_barrier(0);
       }
     };
@@ -680,6 +695,260 @@ __global__ __launch_bounds__(192 * ROT) __attribute__((amdgpu_waves_per_eu(2))) 
       I.out[jj] = jj == 0 ? A[-RING_N] : A[RING_N - jj];
     if (j == 0 && lane == 0) I.out[RING_N] = s_acc[rot_i][1][0];
   }
+}
+
+// ---------------------------------------------------------------------------
+// Blind rotation, six wavefronts per rotation (br6_kernel), one rotation per
+// workgroup and CU, for rounds of at most one per CU: wavefront w transforms
+// row w (digit w / 2 of polynomial w mod 2) and leaves it in LDS; then half hf
+// (i8) of channel ch of the products and of the inverse transform belong to
+// wavefront 3 hf + ch; the halves meet in the last stage and the packed
+// channel's integers go to the other four through LDS.  Four barriers per
+// step.  Bound: the latency of that chain (660 VALU instructions per wavefront,
+// two SIMDs carry two of the six); twiddles stay in registers and the step's
+// 24 key values per lane are loaded a step ahead.  One rotation takes 2.77 ms,
+// 256 take 2.78 ms (3.8 ms before, with four wavefronts and two-prime
+// transforms; 3.07 and 3.18 ms with three wavefronts).
+// ---------------------------------------------------------------------------
+constexpr int INV_TW = 8;          // lane twiddles of the half-size inverse, per half
+constexpr int HROW = 17, HCOMP = 16 * HROW;  // its exchange: element e at 17 (e >> 4) + (e & 15)
+
+// 256 of a channel's 512 values (i8 fixed), four registers per lane.
+struct HalfTw {
+  double r[INV_TW], i[INV_TW];
+};
+__device__ __forceinline__ void swap_half(Cplx (&z)[4]) {  // register bit 1 <-> lane bit 5, bit 0 <-> lane bit 4
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    swap_lane(z[m].r, z[m + 2].r, false);
+    swap_lane(z[m].i, z[m + 2].i, false);
+  }
+#pragma unroll
+  for (int m = 0; m < 4; m += 2) {
+    swap_lane(z[m].r, z[m + 1].r, true);
+    swap_lane(z[m].i, z[m + 1].i, true);
+  }
+}
+// Two stages: register bit 0 (twiddle e, I times it where register bit 1 is set), then bit 1 (twiddle e + 1).
+__device__ __forceinline__ void inv_half2(Cplx (&z)[4], const HalfTw& t, int e) {
+  bf_inv<false>(z[0], z[1], t.r[e], t.i[e]);
+  bf_inv<true>(z[2], z[3], t.r[e], t.i[e]);
+  bf_inv<false>(z[0], z[2], t.r[e + 1], t.i[e + 1]);
+  bf_inv<false>(z[1], z[3], t.r[e + 1], t.i[e + 1]);
+}
+
+__global__ __launch_bounds__(384) __attribute__((amdgpu_waves_per_eu(2))) void br6_kernel(
+    const BrItem* __restrict__ items, uint32_t count, const FftTables* __restrict__ tables) {
+  __shared__ double s_x[6][2 * XPOLY];  // forward exchange, then the transformed digits; then the packed integers
+  __shared__ double s_h[6][2 * HCOMP];  // inverse exchanges
+  __shared__ uint32_t s_acc[2][3 * RING_N];  // each polynomial p as the window p, -p, p
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int j = w >> 1, c = w & 1;         // forward: digit j of polynomial c
+  const int hf = w >= 3, ch = w - 3 * hf;  // products and inverse: half hf (i8) of channel ch
+  const BrItem I = items[blockIdx.x];
+  // Twiddles in registers for the whole rotation.
+  const double2* lt = reinterpret_cast<const double2*>(tables->lane) + lane;
+  const TwA ta = load_twa(lt);
+  const TwB tb = load_twb(lt);
+  const TwC tc = load_twc(lt);
+  HalfTw th;
+#pragma unroll
+  for (int e = 0; e < INV_TW; ++e) {
+    th.r[e] = tables->half[hf][e][lane][0];
+    th.i[e] = tables->half[hf][e][lane][1];
+  }
+  if (w < 4) {  // acc = (0, X^(-bbar) * mu * (1 + X + ... + X^1023)): four wavefronts, half a polynomial each
+    const uint32_t bbar = __builtin_amdgcn_readfirstlane(abar_of(I, LWE_n));
+    const uint32_t rot = (2048u - bbar) & 2047u;
+#pragma unroll
+    for (int R = 0; R < 8; ++R) {
+      const uint32_t jj = 512 * (w & 1) + 64 * R + lane;
+      const bool neg = (jj < (rot & 1023u)) != (rot >= 1024u);
+      const uint32_t v = w < 2 ? 0u : (neg ? (0u - I.mu) : I.mu);
+      uint32_t* p = s_acc[w >> 1] + jj;
+      p[0] = p[2 * RING_N] = v;
+      p[RING_N] = 0u - v;
+    }
+  }
+  const unsigned shift = 32 - BG_BIT * (j + 1);
+  const uint32_t offset = (1u << 10) + (j < 2 ? 1u << 17 : 0u) + (j < 1 ? 1u << 24 : 0u);
+  const double magic = 6755399441055744.0;  // 1.5 * 2^52
+  // Layout 4 backwards: register (i8 i6 i5), lane (i7 | l): row R = 8 i8 + 4 i7 + 2 i6 + i5, +16 for the imaginary part.
+  const uint32_t* acc = s_acc[c] + 128 * (lane >> 5) + (lane & 31);
+  double* xw = s_x[w] + XROW * 8 * (lane >> 5) + (lane & 31);
+  const double* xr = s_x[w] + XROW * (lane & 15) + ((lane >> 5) << 1) + ((lane >> 4) & 1);
+  double2* dw = reinterpret_cast<double2*>(s_x[w]) + lane;
+  // Half layout: register (i1 i0), lane (i3 i2 | i4 | i7 i6 i5); stored index m 64 + lane' of layout 3.
+  const int at = ((lane >> 4) & 1) * 64 + ((lane >> 3) & 1) * 32 + (lane >> 5) * 16 + hf * 8 + (lane & 7);
+  const double2* dr = reinterpret_cast<const double2*>(s_x[0]) + at;
+  constexpr int DROW = XPOLY;  // double2 between rows of s_x
+  // Half exchange: write register (i3 i2), lane (i1 i0 | i4 | i7 i6 i5); read register (i5 i4), lane (i7 i6 | i3..i0).
+  double* hw = s_h[w] + HROW * (2 * (lane & 7) + ((lane >> 3) & 1)) + ((lane >> 5) << 1) + ((lane >> 4) & 1);
+  const double* hr = s_h[w] + HROW * (8 * (lane >> 5) + 4 * ((lane >> 4) & 1)) + (lane & 15);
+  double2* pw = reinterpret_cast<double2*>(s_h[w]) + lane;
+  const double2* pr = reinterpret_cast<const double2*>(s_h[hf ? w - 3 : w + 3]) + lane;
+  uint32_t* lo_words = reinterpret_cast<uint32_t*>(s_x[0]) + 128 * hf + lane;
+  const __amdgpu_buffer_rsrc_t key =
+      __builtin_amdgcn_make_buffer_rsrc((void*)I.bk, 0, (int)BK_FFT_BYTES, 0x00027000);
+  double2 k[6][4];  // the step's 24 key values of this lane
+  auto load = [&](int i, int r) {  // row r: registers (i1 i0) at 0, 128, 256, 384
+    const int o = ((i * 6 + r) * FFT_CHANNELS + ch) * 8192;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      k[r][q] = __builtin_bit_cast(
+          double2, __builtin_amdgcn_raw_buffer_load_b128(key, at * 16 + (q & 1) * 2048, o + (q >> 1) * 4096, 0));
+  };
+#pragma unroll
+  for (int r = 0; r < 6; ++r) load(0, r);
+  uint32_t abars = 0;
+  __syncthreads();
+  for (int i = 0; i < LWE_n; ++i) {
+    if ((i & 63) == 0) abars = i + lane < LWE_n ? abar_of(I, i + lane) : 0u;
+    const uint32_t ab = __builtin_amdgcn_readlane(abars, i & 63);
+    Cplx z[8];
+    {
+      const uint32_t* src = acc + ((0u - ab) & (2 * RING_N - 1));
+      uint32_t v[16], own[16];
+#pragma unroll
+      for (int t = 0; t < 16; ++t) {
+        const int m = t & 7, R = 8 * (m >> 2) + 2 * ((m >> 1) & 1) + (m & 1) + 16 * (t >> 3);
+        v[t] = src[32 * R];
+        own[t] = acc[32 * R];
+      }
+#pragma unroll
+      for (int t = 0; t < 16; ++t) {
+        const uint32_t D = (v[t] - own[t]) + offset;
+        (t < 8 ? z[t & 7].r : z[t & 7].i) = (double)(int)__builtin_amdgcn_sbfe(D, shift, (unsigned)BG_BIT);
+      }
+    }
+    // Stage 0, register bit 2 (i8) <-> lane bit 5 (i7), stages 1-3.
+#pragma unroll
+    for (int m = 0; m < 4; ++m) bf_fwd<false>(z[m], z[m + 4], W_RE[0], W_IM[0]);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      swap_lane(z[m].r, z[m + 4].r, false);
+      swap_lane(z[m].i, z[m + 4].i, false);
+    }
+    fwd_stages123(z, tc);
+    wave_lds_sync();
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      xw[XROW * m] = z[m].r;
+      xw[XPOLY + XROW * m] = z[m].i;
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      z[m].r = xr[4 * m];
+      z[m].i = xr[XPOLY + 4 * m];
+    }
+    wave_lds_sync();
+    fwd_stages456(z, ta);
+    swap_23(z);
+    fwd_stages78(z, tb);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) dw[64 * m] = make_double2(z[m].r, z[m].i);
+    __syncthreads();
+    // Products of this half of the channel with all six rows.
+    Cplx s[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s[q] = {0.0, 0.0};
+    const int next = i + 1 < LWE_n ? i + 1 : i;
+#pragma unroll
+    for (int r = 0; r < 6; ++r) {
+      double2 d[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) d[q] = dr[DROW * r + 128 * q];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        s[q].r = __builtin_fma(d[q].x, k[r][q].x, s[q].r);
+        s[q].i = __builtin_fma(d[q].x, k[r][q].y, s[q].i);
+        s[q].r = __builtin_fma(-d[q].y, k[r][q].y, s[q].r);
+        s[q].i = __builtin_fma(d[q].y, k[r][q].x, s[q].i);
+      }
+      load(next, r);
+    }
+    inv_half2(s, th, 0);
+    swap_half(s);
+    inv_half2(s, th, 2);
+    wave_lds_sync();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {  // element: row i7..i4, column i3..i0
+      hw[4 * q] = s[q].r;
+      hw[HCOMP + 4 * q] = s[q].i;
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      s[q].r = hr[HROW * q];
+      s[q].i = hr[HCOMP + HROW * q];
+    }
+    wave_lds_sync();
+    inv_half2(s, th, 4);
+    swap_half(s);
+    inv_half2(s, th, 6);
+    // Stage 0 joins the halves: this wavefront takes the positions with i7 = hf.
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const Cplx& g = hf ? s[q] : s[2 + q];
+      pw[64 * q] = make_double2(g.r, g.i);
+    }
+    __syncthreads();
+    Cplx o[4];  // (i8 i6)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const double2 g = pr[64 * q];
+      const Cplx other{g.x, g.y}, keep = hf ? s[2 + q] : s[q];
+      o[q] = hf ? other : keep;
+      o[2 + q] = hf ? keep : other;
+      bf_inv<false>(o[q], o[2 + q], W_RE[0], W_IM[0]);
+    }
+    // Coefficient 256 i8 + 128 hf + 64 i6 + lane, +512 for the imaginary part.
+    uint32_t x[8];
+    uint32_t* ap = s_acc[ch & 1] + 128 * hf + lane;
+    if (ch == 2) {
+      constexpr double half = (double)(1 << (LO_SHIFT - 1));
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const double f = t < 4 ? o[t & 3].r : o[t & 3].i;
+        const int J = 256 * ((t >> 1) & 1) + 64 * (t & 1) + 512 * (t >> 2);
+        const uint32_t wa = (uint32_t)__builtin_bit_cast(uint64_t, f + magic);
+        const uint64_t wb = __builtin_bit_cast(uint64_t, f + (magic + half));
+        lo_words[J] = __builtin_amdgcn_sbfe(wa, 0u, (unsigned)LO_SHIFT);
+        lo_words[1024 + J] = __builtin_amdgcn_sbfe(
+            __builtin_amdgcn_alignbit((uint32_t)(wb >> 32), (uint32_t)wb, LO_SHIFT), 0u, (unsigned)LO_SHIFT);
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int J = 256 * ((t >> 1) & 1) + 64 * (t & 1) + 512 * (t >> 2);
+        const uint32_t h = (uint32_t)__builtin_bit_cast(uint64_t, (t < 4 ? o[t & 3].r : o[t & 3].i) + magic);
+        uint32_t h5 = (h << 2) + h;
+        asm("" : "+v"(h5));
+        x[t] = ap[J] + (h5 << 2);
+      }
+    }
+    __syncthreads();
+    if (ch < 2) {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int J = 256 * ((t >> 1) & 1) + 64 * (t & 1) + 512 * (t >> 2);
+        x[t] += lo_words[1024 * ch + J];
+      }
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int J = 256 * ((t >> 1) & 1) + 64 * (t & 1) + 512 * (t >> 2);
+        ap[J] = ap[2 * RING_N + J] = x[t];
+        ap[RING_N + J] = 0u - x[t];
+      }
+    }
+    __syncthreads();
+  }
+  // SampleExtract: a'_0 = A_0, a'_j = -A_(N-j), b' = B_0.
+  const uint32_t* A = s_acc[0] + RING_N;  // -A
+  for (int jj = (int)threadIdx.x; jj < RING_N; jj += 384) I.out[jj] = jj == 0 ? A[-RING_N] : A[RING_N - jj];
+  if (threadIdx.x == 0) I.out[RING_N] = s_acc[1][0];
 }
 
 // ---------------------------------------------------------------------------
@@ -986,8 +1255,8 @@ int launch_br(const BrItem* items, uint32_t count, const FftTables* tables, uint
     case 16 + 2: hipLaunchKernelGGL(br1_kernel<2>, grid, block, 0, S(stream), items, count, tw); break;
     case 16 + 4: hipLaunchKernelGGL(br1_kernel<4>, grid, block, 0, S(stream), items, count, tw); break;
     case 16 + 8: hipLaunchKernelGGL(br1_kernel<8>, grid, block, 0, S(stream), items, count, tw); break;
-    case 48 + 1: hipLaunchKernelGGL((br3_kernel<1, 3>), grid, block, 0, S(stream), items, count, tw); break;
-    case 48 + 2: hipLaunchKernelGGL((br3_kernel<2, 1>), grid, block, 0, S(stream), items, count, tw); break;
+    case 48 + 2: hipLaunchKernelGGL(br3_kernel, grid, block, 0, S(stream), items, count, tw); break;
+    case 96 + 1: hipLaunchKernelGGL(br6_kernel, grid, block, 0, S(stream), items, count, tables); break;
     default: return (int)hipErrorInvalidValue;
   }
   return (int)hipGetLastError();

@@ -183,12 +183,12 @@ void mark_end(vlp_ctx* ctx, int id, int kind, uint64_t items);
 // L2 once for many of them (a persistent loop over many rounds let them drift
 // apart and re-fetch it).
 // Automatic mode picks each round by what is left, in rotations per CU, from
-// the measured times of a round: up to 1 per CU 3.3 ms (three wavefronts, one
-// rotation per workgroup), up to 2 4.5 ms (three wavefronts, two), up to 4
-// 7.5 ms (one wavefront each, one per SIMD), up to 8 12.0 ms (two per SIMD).
-// So the smallest round that holds the rest, except that 4 to 5 per CU run as
-// 4 and 1 (10.8 ms); splitting the others gains nothing (3 as 2 and 1: 7.8 ms;
-// 6 as 4 and 2: 12.0 ms).
+// the measured times of a round: up to 1 per CU 2.8 ms (six wavefronts per
+// rotation), up to 2 4.4 ms (three), up to 4 7.5 ms (one each, one per SIMD),
+// up to 8 12.2 ms (two per SIMD).  So the smallest round that holds the rest,
+// except that 4 to 5 per CU run as 4 and 1 (10.3 ms) and 5 to 6 as 4 and 2
+// (11.9 ms); splitting the others gains nothing (2 as 1 and 1: 5.5 ms; 3 as 2
+// and 1: 7.2 ms, within a box's spread of 7.5; 7 as 4, 2 and 1: 14.7 ms).
 struct BrRound {
   uint32_t waves, rot_per_block, rotations;
 };
@@ -196,13 +196,13 @@ BrRound next_round(const vlp_tuning& t, uint32_t cus, uint32_t left) {
   const uint32_t rpb = t.br_rotations_per_block, bpc = t.br_blocks_per_cu;
   switch (t.br_waves_per_rotation) {
     case 1: return {1, rpb, cus * bpc * rpb};
-    case 2: return {3, std::min(rpb, 2u), cus * bpc * rpb};
-    case 4: return {3, 1, cus * bpc};
+    case 2: return {rpb == 1 ? 6u : 3u, std::min(rpb, 2u), cus * bpc * rpb};
+    case 4: return {6, 1, cus * bpc};
     default: break;
   }
-  if (left <= cus) return {3, 1, cus};
+  if (left <= cus) return {6, 1, cus};
   if (left <= 2 * cus) return {3, 2, 2 * cus};
-  if (left <= 5 * cus) return {1, 4, 4 * cus};
+  if (left <= 6 * cus) return {1, 4, 4 * cus};
   return {1, 8, 8 * cus};
 }
 
