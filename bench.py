@@ -339,13 +339,13 @@ def server_enc_bench(args):
     ctx.close()
 
 
-# Key switching on the matrix cores: per gate, a product of the one-hot digit
-# matrix (1,024 coefficients x 8 levels x 4 digit values = 32,768 columns)
-# with the key's 4 byte planes of 640 (631 padded) words, 2 ops per
-# multiply-add; dense int8 peak of MI355X 5.0 POP/s.  The method's own work is
-# at most 8,192 row subtractions of 631 words (5,169,152 adds; 3/4 of that on
-# average for uniform digits).
-KS_MFMA_OPS = 2 * 1024 * 8 * 4 * 640 * 4  # 167,772,160
+# Key switching on the matrix cores: per gate, a product of a 0/1 matrix of the
+# digits' bits (1,024 coefficients x 8 levels x 3 columns = 24,576) with the
+# key's 4 byte planes of 640 (631 padded) words, 2 ops per multiply-add; dense
+# int8 peak of MI355X 5.0 POP/s.  The method's own work is at most 8,192 row
+# subtractions of 631 words (5,169,152 adds; 3/4 of that on average for
+# uniform digits).
+KS_MFMA_OPS = 2 * 1024 * 8 * 3 * 640 * 4  # 125,829,120
 PEAK_INT8_OPS = 5.0e15
 KS_ADDS_MAX = 1024 * 8 * 631
 
@@ -392,7 +392,7 @@ def keyswitch_bench(args):
         "roofline": {"bound": "mfma", "achieved": ops / 1e12, "peak": PEAK_INT8_OPS / 1e12, "unit": "TOP/s (int8)",
                      "frac": ops / PEAK_INT8_OPS, "traffic": None, "mfma_ops_per_key_switch": KS_MFMA_OPS},
         "algorithmic": {"adds_per_s_max": KS_ADDS_MAX * rate, "adds_per_s_mean": 0.75 * KS_ADDS_MAX * rate,
-                        "key_bytes_per_call": 83886080 * -(-B // 16384)},
+                        "key_bytes_per_call": 62914560 * -(-B // 16384)},
     }), flush=True)
     ctx.close()
 

@@ -137,7 +137,7 @@ vlp_status vlp_mem_info(const vlp_ctx *ctx, size_t *used, size_t *budget);
  * work and may be freed after vlp_sync().  The keyset holds the bootstrapping
  * key transformed for the exact negacyclic products (92,905,472 B) and the
  * key-switching key as signed byte planes for the 8-bit matrix cores
- * (83,886,080 B).  VLP_EBUDGET if it does not fit. */
+ * (62,914,560 B).  VLP_EBUDGET if it does not fit. */
 vlp_status vlp_keyset_load(vlp_ctx *ctx, const uint32_t *bk_dev, const uint32_t *ksk_dev, vlp_keyset **out);
 
 /* Frees a keyset (VLP_EBUSY while programs made with it are alive). */
@@ -168,7 +168,7 @@ vlp_status vlp_gate(vlp_ctx *ctx, const vlp_keyset *ks, vlp_gate_op op, const ui
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
  * same gates, bit for bit, with the intermediate ciphertexts and work items
  * in a fixed scratch array that the library holds on each device for the
- * life of the process (10,665,984 B), so the call makes no hipMalloc/hipFree.
+ * life of the process (10,625,024 B), so the call makes no hipMalloc/hipFree.
  * B <= 1024 gates per call (VLP_EINVAL above that).  Every call on one
  * device shares that device's array: calls that overlap in time on the same
  * device (two contexts or two streams) race and give wrong results; calls

@@ -22,14 +22,19 @@ constexpr uint32_t MU = 0x20000000u; // 1/8
 // order (layout 3, so a wavefront's loads are contiguous), scaled by 1/512.
 constexpr size_t BK_ROW_POINTS = (size_t)2 * ELL * 3 * (RING_N / 2);  // complex points of one key row i
 constexpr size_t BK_FFT_BYTES = (size_t)LWE_n * BK_ROW_POINTS * 16 + 8192;  // + one batch that is read ahead, not used
-// Key-switching key laid out for the 8-bit matrix cores, as byte planes:
-// [1024 coefficients i][20 tiles of 32 output words][4 byte planes p][64
-// lanes][4 words t].  Lane n + 32 h, word t holds, for output word
-// 32 * tile + n and level j = 4 h + t, byte p of the entries [i][j][v] for
-// v = 0..3 in bytes v = 0..3, each XOR 0x80 (a signed byte: value - 128); the
-// entry v = 0 and the words past 630 are zero.
-constexpr int KS_TILES = 20;                                        // 640 words / 32
-constexpr size_t KSK_WORDS = (size_t)RING_N * KS_TILES * 4 * 64 * 4;  // u32 words (83,886,080 B)
+// Key-switching key laid out for the 8-bit matrix cores: for every coefficient
+// i and level j the three words F_0 = K_1, F_1 = K_2, F_2 = K_3 - K_1 - K_2 of
+// its entries K_v = [i][j][v] (mod 2^32; the entry v = 0 is ignored), so that
+// K_d = b0 F_0 + b1 F_1 + b0 b1 F_2 for the bits b0, b1 of a digit d.  Each
+// word as four signed bytes (F = sum_p 2^(8p) s_p mod 2^32, s_p in [-128,
+// 127]).  [256 groups of 4 coefficients][20 tiles of 32 output words][3
+// blocks][4 byte planes p][64 lanes][4 words]: lane n + 32 h, word d' = 4 block
+// + word = 3 t + f holds, for output word 32 tile + n and level j = 4 h + t,
+// byte s_p of F_f of the group's coefficients 0..3 in bytes 0..3; words past
+// 630 are zero.
+constexpr int KS_TILES = 20;                                           // 640 words / 32
+constexpr int KS_GROUPS = RING_N / 4;
+constexpr size_t KSK_WORDS = (size_t)KS_GROUPS * KS_TILES * 3 * 4 * 64 * 4;  // u32 words (62,914,560 B)
 
 // One blind rotation: input = (0, cst) + ca * a + cb * b + cm * (more[0] +
 // ... + more[n_more - 1]), output the sample-extracted LWE_N ciphertext of
@@ -56,15 +61,22 @@ struct KsItem {
   uint32_t pad;
 };
 
+// The key switches of a launch: an array of items in device memory, or (items
+// null) elementwise ones, item t being `first` with its ciphertexts advanced t
+// places.
+struct KsSource {
+  const KsItem* items;
+  KsItem first;
+};
+
 // Fixed device scratch of the allocation-free gate call (vlp_gate_noalloc):
 // the sample-extracted outputs of up to 2 blind rotations per gate, then the
-// blind-rotation and key-switching work items and the key-switching digits
-// (2 KiB per gate), for at most
-// NOALLOC_MAX_GATES gates per call.  One copy per device, in kernels.hip.
+// blind-rotation work items and the key-switching digits (2 KiB per gate), for
+// at most NOALLOC_MAX_GATES gates per call.  One copy per device, in kernels.hip.
 constexpr size_t NOALLOC_MAX_GATES = 1024;
 constexpr size_t NOALLOC_EXT_BYTES = 2 * NOALLOC_MAX_GATES * CT_N * 4;   // multiple of 256
 constexpr size_t NOALLOC_BYTES = NOALLOC_EXT_BYTES + 2 * NOALLOC_MAX_GATES * sizeof(BrItem) +
-                                 NOALLOC_MAX_GATES * sizeof(KsItem) + NOALLOC_MAX_GATES * RING_N * 2;
+                                 NOALLOC_MAX_GATES * RING_N * 2;
 // Device address of the current device's copy of that scratch (the HIP error
 // of the lookup; call with the device current).
 int noalloc_scratch_address(void** p);
@@ -96,12 +108,10 @@ int launch_server_enc(const uint32_t* pk, uint32_t* out, size_t count, const int
 // the device's CUs.
 constexpr uint32_t KS_CHUNK = 16384;
 constexpr size_t ks_digit_bytes(size_t count) { return (count < KS_CHUNK ? count : KS_CHUNK) * (RING_N * 2); }
-int launch_ks_group(const KsItem* items, uint32_t count, const uint32_t* ksk, uint32_t* dig,
+int launch_ks_group(const KsSource& src, uint32_t count, const uint32_t* ksk, uint32_t* dig,
                     uint32_t gates_per_block, uint32_t cus, void* stream);
 int launch_make_br_items(BrItem* items, uint32_t count, const uint32_t* a, const uint32_t* b, int32_t ca, int32_t cb,
                          uint32_t cst, uint32_t mu, uint32_t* out, const void* bk, void* stream);
-int launch_make_ks_items(KsItem* items, uint32_t count, const uint32_t* u1, const uint32_t* u2, uint32_t cst,
-                         uint32_t* out, const uint32_t* ksk, void* stream);
 int launch_negate(const uint32_t* a, uint32_t* out, size_t words, void* stream);
 
 }  // namespace vlp

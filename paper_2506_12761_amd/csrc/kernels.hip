@@ -14,6 +14,15 @@ namespace vlp {
 // loads, so they are not counted by the LDS wait of the transposes.
 typedef const uint32_t __attribute__((address_space(1))) g_u32;
 
+__device__ __forceinline__ KsItem ks_item(const KsSource& src, uint32_t t) {
+  if (src.items) return src.items[t];
+  KsItem it = src.first;
+  it.u1 += (size_t)t * CT_N;
+  if (it.u2) it.u2 += (size_t)t * CT_N;
+  it.out += (size_t)t * CT_n;
+  return it;
+}
+
 // ---------------------------------------------------------------------------
 // Key preparation
 // ---------------------------------------------------------------------------
@@ -87,22 +96,42 @@ __global__ __launch_bounds__(256) void bk_transform_kernel(const uint32_t* __res
   }
 }
 
-// The key-switching key [1024][8][4][631] in the byte-plane layout of
-// KSK_WORDS (internal.h), one output word per thread.
-__global__ void ksk_relayout_kernel(const uint32_t* __restrict__ in, uint32_t* __restrict__ out) {
-  for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < KSK_WORDS;
-       idx += (size_t)gridDim.x * blockDim.x) {
-    const uint32_t t = idx & 3, lane = (idx >> 2) & 63, p = (idx >> 8) & 3;
-    const size_t rest = idx >> 10;
-    const uint32_t tile = (uint32_t)(rest % KS_TILES), i = (uint32_t)(rest / KS_TILES);
-    const uint32_t j = 4 * (lane >> 5) + t, w = 32 * tile + (lane & 31);
-    uint32_t word = 0x80u;  // v = 0: the zero entry
-    for (uint32_t v = 1; v < 4; ++v) {
-      const uint32_t k = w < (uint32_t)CT_n ? in[(((size_t)i * KS_T + j) * 4 + v) * CT_n + w] : 0u;
-      word |= (((k >> (8 * p)) & 0xFFu) ^ 0x80u) << (8 * v);
+// The key-switching key [1024][8][4][631] in the layout of KSK_WORDS
+// (internal.h).  One thread per (group, tile, lane): it reads that output
+// word's entries of 4 coefficients and 4 levels and writes their bytes as 12
+// words of 16 bytes, a run of 1 KiB per wavefront each.
+__global__ __launch_bounds__(256) void ksk_relayout_kernel(const uint32_t* __restrict__ in, uint4* __restrict__ out) {
+  const uint32_t lane = threadIdx.x & 63, tile = blockIdx.x, q = blockIdx.y * 4 + (threadIdx.x >> 6);
+  const uint32_t w = 32 * tile + (lane & 31), h = lane >> 5;
+  uint32_t b[3][4][4] = {};  // [block][plane][word]
+#pragma unroll
+  for (uint32_t c = 0; c < 4; ++c)
+#pragma unroll
+    for (uint32_t t = 0; t < 4; ++t) {
+      uint32_t f[3] = {0, 0, 0};
+      if (w < (uint32_t)CT_n) {
+        const uint32_t* k = in + (size_t)((4 * q + c) * KS_T + 4 * h + t) * 4 * CT_n + w;
+        f[0] = k[CT_n];
+        f[1] = k[2 * CT_n];
+        f[2] = k[3 * CT_n] - f[0] - f[1];
+      }
+#pragma unroll
+      for (uint32_t n = 0; n < 3; ++n) {
+        const uint32_t d = 3 * t + n;
+        uint32_t v = f[n];
+#pragma unroll
+        for (uint32_t p = 0; p < 4; ++p) {
+          const int32_t s = (int8_t)(v & 0xFFu);
+          b[d >> 2][p][d & 3] |= (uint32_t)(uint8_t)s << (8 * c);
+          v = (v - (uint32_t)s) >> 8;
+        }
+      }
     }
-    out[idx] = word;
-  }
+  uint4* o = out + (size_t)(q * KS_TILES + tile) * (3 * 4 * 64) + lane;
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+#pragma unroll
+    for (int p = 0; p < 4; ++p) o[(k * 4 + p) * 64] = make_uint4(b[k][p][0], b[k][p][1], b[k][p][2], b[k][p][3]);
 }
 
 // ---------------------------------------------------------------------------
@@ -955,23 +984,25 @@ __global__ __launch_bounds__(384) __attribute__((amdgpu_waves_per_eu(2))) void b
 // Key switching on the 8-bit matrix cores.
 //
 // The key switch of gate g subtracts, for every coefficient i < 1024 and
-// level j < 8, the key entry selected by the digit d_ij of a'_i + 2^15.  With
-// A[g][(i, j, v)] = [d_ij = v] (exactly one 1 per (i, j), the entry v = 0
-// being zero) that sum is the product A x K of the one-hot matrix and the key
-// K[(i, j, v)][w]; split K into byte planes K_p (so K = sum_p 2^(8p) K_p) and
-// each plane's product is an exact integer (at most 8,192 terms below 2^8),
-// computed by v_mfma_i32_32x32x32_i8 on signed bytes K_p - 128 (stored XOR
-// 0x80); every (i, j) contributes exactly one -128, so the word is
-// sum_p 2^(8p) C_p + 128 x (pairs) x 0x01010101 (mod 2^32).
+// level j < 8, the key entry K_d of the digit d = d_ij of a'_i + 2^15.  With
+// the bits of d, K_d = b0 F_0 + b1 F_1 + b0 b1 F_2 (internal.h), so the sum is
+// the product A x F of a 0/1 matrix of 3 columns per (i, j) and the words F;
+// split into signed byte planes (F = sum_p 2^(8p) F_p mod 2^32) each plane's
+// product is an exact integer (at most 24,576 terms of magnitude <= 128),
+// computed by v_mfma_i32_32x32x32_i8, and the word is sum_p 2^(8p) C_p.  (One
+// column per digit value, the zero entry included, takes a third more matrix
+// work and key bytes, and a correction for unsigned bytes.)
 //
-// K-block of one MFMA = one coefficient i: lane n + 32 h supplies, in its 16
-// operand bytes t*4 + v, the levels j = 4 h + t and the digit values v (the
-// key lane of the same index supplies the same (j, v)); the gate rows of the
-// A operand are the lanes' n, the output words of the B operand the lanes' n.
-// A workgroup of 4 wavefronts covers 4 x RT x 32 gates and one tile of 32
-// output words (4 planes = 4 accumulators per 32 gates); blockIdx.z takes a
-// range of coefficients, whose partial results are added atomically into
-// outputs zeroed first when there is more than one range.
+// Four coefficients make three MFMA K-blocks: lane n + 32 h supplies for the
+// levels j = 4 h + t the words d' = 3 t + f, byte c for coefficient c; with
+// the group's digit bytes in one register x (byte c = digits of coefficient c,
+// level t in bits 6 - 2t), b0 and b1 of all four are a shift and a mask each.
+// The gate rows of the A operand are the lanes' n, the output words of the B
+// operand the lanes' n.  A workgroup of 4 wavefronts covers 4 x RT x 32 gates
+// and one tile of 32 output words (4 planes = 4 accumulators per 32 gates), or,
+// SPLIT, RT x 32 gates with a quarter of the coefficients per wavefront, summed
+// in LDS; blockIdx.z takes a range of coefficients, whose partial results are
+// added atomically into outputs zeroed first when there is more than one range.
 // ---------------------------------------------------------------------------
 typedef int v16i __attribute__((ext_vector_type(16)));
 
@@ -979,15 +1010,22 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 // dig[(q * count + g) * 2 + h], byte c = bits [24 - 8h, 32 - 8h) of
 // a'_(4q+c) + 2^15, i.e. the digits of levels 4h .. 4h + 3 of coefficient
 // 4q + c, most significant first.  With zero_out the outputs are cleared
-// (split key switching adds into them).  One thread per (q, g), g fastest.
-__global__ void ks_prep_kernel(const KsItem* __restrict__ items, uint32_t count, uint2* __restrict__ dig,
-                               int zero_out) {
-  const size_t total = (size_t)count * (RING_N / 4);
-  for (size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (size_t)gridDim.x * blockDim.x) {
-    const uint32_t g = (uint32_t)(t % count), q = (uint32_t)(t / count);
-    const KsItem& it = items[g];
-    const g_u32* u1 = (const g_u32*)it.u1 + 4 * q;
-    const g_u32* u2 = it.u2 ? (const g_u32*)it.u2 + 4 * q : nullptr;
+// (split key switching adds into them).  A workgroup turns a tile of 64 gates
+// x 16 groups through LDS: 256-byte runs of a gate are read, 512-byte runs of
+// a group written (one thread per (group, gate) read a gate's 16 bytes beside
+// 63 others': 16,384 gates 94 us, now 31).
+constexpr int PREP_G = 64, PREP_Q = 16;
+__global__ __launch_bounds__(256) void ks_prep_kernel(KsSource src, uint32_t from, uint32_t count,
+                                                      uint2* __restrict__ dig, int zero_out) {
+  __shared__ uint2 s[PREP_Q][PREP_G + 1];
+  const uint32_t g0 = blockIdx.x * PREP_G, q0 = blockIdx.y * PREP_Q;
+  const uint32_t q = threadIdx.x & 15;
+  for (uint32_t r = threadIdx.x >> 4; r < PREP_G; r += 16) {
+    const uint32_t g = g0 + r;
+    if (g >= count) break;
+    const KsItem it = ks_item(src, from + g);
+    const g_u32* u1 = (const g_u32*)it.u1 + 4 * (q0 + q);
+    const g_u32* u2 = it.u2 ? (const g_u32*)it.u2 + 4 * (q0 + q) : nullptr;
     uint32_t hi = 0, lo = 0;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -995,40 +1033,46 @@ __global__ void ks_prep_kernel(const KsItem* __restrict__ items, uint32_t count,
       hi |= (a >> 24) << (8 * c);
       lo |= ((a >> 16) & 0xFFu) << (8 * c);
     }
-    dig[t] = make_uint2(hi, lo);
-    if (zero_out && 4 * q < (uint32_t)CT_n)
+    s[q][r] = make_uint2(hi, lo);
+    if (zero_out)
 #pragma unroll
       for (int c = 0; c < 4; ++c)
-        if (4 * q + c < (uint32_t)CT_n) it.out[4 * q + c] = 0u;
+        if (4 * (q0 + q) + c < (uint32_t)CT_n) it.out[4 * (q0 + q) + c] = 0u;
+  }
+  __syncthreads();
+  for (uint32_t t = threadIdx.x; t < PREP_G * PREP_Q; t += 256) {
+    const uint32_t g = g0 + t % PREP_G, k = t / PREP_G;
+    if (g < count) dig[(size_t)(q0 + k) * count + g] = s[k][t % PREP_G];
   }
 }
 
-template <int RT>
+template <int RT, bool SPLIT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4 / RT))) void ks_mfma_kernel(
-    const KsItem* __restrict__ items, uint32_t count,
-                                                      const uint32_t* __restrict__ dig,
-                                                      const uint4* __restrict__ ksk, uint32_t i_per_block) {
+    KsSource src, uint32_t from, uint32_t count, const uint32_t* __restrict__ dig, const uint4* __restrict__ ksk,
+    uint32_t groups_per_block) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t tile = blockIdx.x;
-  const uint32_t row0 = (blockIdx.y * 4 + wave) * (RT * 32);
-  const uint32_t i0 = blockIdx.z * i_per_block, i_end = i0 + i_per_block;
+  const uint32_t row0 = (SPLIT ? blockIdx.y : blockIdx.y * 4 + wave) * (RT * 32);
+  const uint32_t per_wave = SPLIT ? groups_per_block / 4 : groups_per_block;
+  const uint32_t q_begin = blockIdx.z * groups_per_block + (SPLIT ? wave * per_wave : 0), q_end = q_begin + per_wave;
   const int n = lane & 31, h = lane >> 5;
   // Digit words of this lane's gate rows (rows past the last gate read the
   // last gate's digits; their results are not stored).
   const g_u32* dp[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) dp[rt] = (const g_u32*)dig + (size_t)min(row0 + rt * 32 + n, count - 1) * 2 + h;
-  const size_t dstep = (size_t)count * 2;  // words between coefficient groups
+  const size_t dstep = (size_t)count * 2;  // words between groups
   v16i acc[RT][4];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int p = 0; p < 4; ++p) acc[rt][p] = v16i{};
-  // Key fragments of coefficient i: kb + i * KS_TILES * 256 (4 planes x 64 lanes).
-  const g_u32* kb = (const g_u32*)(ksk + (size_t)tile * 256 + lane);
-  auto load_b = [&](uint32_t i, v4i* b) {
-    const uint4* k = (const uint4*)(kb) + (size_t)i * KS_TILES * 256;
+  // Key fragments: [group][tile][3 blocks][4 planes][64 lanes], one block of
+  // four loaded a block ahead of its use.
+  const uint4* kb = ksk + (size_t)tile * (3 * 256) + lane;
+  auto load_b = [&](uint32_t q, int block, v4i (&b)[4]) {
+    const uint4* k = kb + (size_t)q * (KS_TILES * 3 * 256) + block * 256;
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
       const uint4 v = k[p * 64];
@@ -1037,55 +1081,70 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4 / RT))) v
   };
   uint32_t dcur[RT], dnext[RT];
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt) dcur[rt] = dp[rt][(size_t)(i0 / 4) * dstep];
-  v4i b0[4], b1[4];
-  load_b(i0, b0);
-  load_b(i0 + 1, b1);
-  for (uint32_t q = i0 / 4; q < i_end / 4; ++q) {
-    const uint32_t qn = min(q + 1, i_end / 4 - 1);
+  for (int rt = 0; rt < RT; ++rt) dcur[rt] = dp[rt][(size_t)q_begin * dstep];
+  v4i b[3][4];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) load_b(q_begin, k, b[k]);
+  for (uint32_t q = q_begin; q < q_end; ++q) {
+    const uint32_t qn = min(q + 1, q_end - 1);
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) dnext[rt] = dp[rt][(size_t)qn * dstep];
+    int a[RT][12];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      v4i b[4];
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        b[p] = b0[p];
-        b0[p] = b1[p];
+      for (int t = 0; t < 4; ++t) {
+        const uint32_t b0 = (dcur[rt] >> (6 - 2 * t)) & 0x01010101u, b1 = (dcur[rt] >> (7 - 2 * t)) & 0x01010101u;
+        a[rt][3 * t] = (int)b0;
+        a[rt][3 * t + 1] = (int)b1;
+        a[rt][3 * t + 2] = (int)(b0 & b1);
       }
-      load_b(min(4 * q + c + 2, i_end - 1), b1);
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        const uint32_t x = dcur[rt] >> (8 * c);
-        v4i a;
+    for (int k = 0; k < 3; ++k) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) a[t] = (int)(1u << (((x >> (6 - 2 * t)) & 3u) << 3));
+      for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-        for (int p = 0; p < 4; ++p) acc[rt][p] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b[p], acc[rt][p], 0, 0, 0);
-      }
+        for (int p = 0; p < 4; ++p)
+          acc[rt][p] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
+              v4i{a[rt][4 * k], a[rt][4 * k + 1], a[rt][4 * k + 2], a[rt][4 * k + 3]}, b[k][p], acc[rt][p], 0, 0, 0);
+      load_b(qn, k, b[k]);
     }
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) dcur[rt] = dnext[rt];
   }
-  const uint32_t corr = 128u * 8u * i_per_block * 0x01010101u;
+  // Result register r of lane n + 32 h: row 8 (r / 4) + 4 h + r mod 4, word n.
   const uint32_t w = tile * 32 + n;
-  if (w >= (uint32_t)CT_n) return;
+  auto store = [&](uint32_t g, uint32_t sum) {
+    if (g >= count || w >= (uint32_t)CT_n) return;
+    const KsItem it = ks_item(src, from + g);
+    uint32_t val = 0u - sum;
+    if (w == (uint32_t)LWE_n && blockIdx.z == 0) val += it.u1[RING_N] + (it.u2 ? it.u2[RING_N] : 0u) + it.cst;
+    if (gridDim.z == 1) it.out[w] = val;
+    else atomicAdd(it.out + w, val);
+  };
+  auto word = [&](int rt, int r) {
+    return (uint32_t)acc[rt][0][r] + ((uint32_t)acc[rt][1][r] << 8) + ((uint32_t)acc[rt][2][r] << 16) +
+           ((uint32_t)acc[rt][3][r] << 24);
+  };
+  if constexpr (SPLIT) {
+    __shared__ uint32_t s_part[4][RT * 16][64];
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const uint32_t g = row0 + rt * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-      if (g >= count) continue;
-      const uint32_t sum = (uint32_t)acc[rt][0][r] + ((uint32_t)acc[rt][1][r] << 8) +
-                           ((uint32_t)acc[rt][2][r] << 16) + ((uint32_t)acc[rt][3][r] << 24) + corr;
-      const KsItem& it = items[g];
-      uint32_t val = 0u - sum;
-      if (w == (uint32_t)LWE_n && blockIdx.z == 0) val += it.u1[RING_N] + (it.u2 ? it.u2[RING_N] : 0u) + it.cst;
-      if (gridDim.z == 1)
-        it.out[w] = val;
-      else
-        atomicAdd(it.out + w, val);
+      for (int r = 0; r < 16; ++r) s_part[wave][rt * 16 + r][lane] = word(rt, r);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < RT * 4; ++k) {
+      const int e = wave * RT * 4 + k, rt = e >> 4, r = e & 15;
+      store(row0 + rt * 32 + 8 * (r >> 2) + 4 * h + (r & 3),
+            s_part[0][e][lane] + s_part[1][e][lane] + s_part[2][e][lane] + s_part[3][e][lane]);
     }
+  } else {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) store(row0 + rt * 32 + 8 * (r >> 2) + 4 * h + (r & 3), word(rt, r));
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1107,20 +1166,6 @@ __global__ void make_br_items_kernel(BrItem* items, uint32_t count, const uint32
   it.more = nullptr;
   it.n_more = 0;
   it.cm = 0;
-  items[t] = it;
-}
-
-__global__ void make_ks_items_kernel(KsItem* items, uint32_t count, const uint32_t* u1, const uint32_t* u2,
-                                     uint32_t cst, uint32_t* out, const uint32_t* ksk) {
-  const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= count) return;
-  KsItem it;
-  it.u1 = u1 + (size_t)t * CT_N;
-  it.u2 = u2 ? u2 + (size_t)t * CT_N : nullptr;
-  it.out = out + (size_t)t * CT_n;
-  it.ksk = ksk;
-  it.cst = cst;
-  it.pad = 0;
   items[t] = it;
 }
 
@@ -1241,7 +1286,8 @@ int launch_bk_transform(const uint32_t* bk_coeff, void* bk_fft, const FftTables*
 }
 
 int launch_ksk_relayout(const uint32_t* ksk_in, uint32_t* ksk_out, void* stream) {
-  hipLaunchKernelGGL(ksk_relayout_kernel, dim3(4096), dim3(256), 0, S(stream), ksk_in, ksk_out);
+  hipLaunchKernelGGL(ksk_relayout_kernel, dim3(KS_TILES, KS_GROUPS / 4), dim3(256), 0, S(stream), ksk_in,
+                     reinterpret_cast<uint4*>(ksk_out));
   return (int)hipGetLastError();
 }
 
@@ -1262,43 +1308,53 @@ int launch_br(const BrItem* items, uint32_t count, const FftTables* tables, uint
   return (int)hipGetLastError();
 }
 
-int launch_ks_group(const KsItem* items, uint32_t count, const uint32_t* ksk, uint32_t* dig,
+int launch_ks_group(const KsSource& src, uint32_t count, const uint32_t* ksk, uint32_t* dig,
                     uint32_t gates_per_block, uint32_t cus, void* stream) {
   if (!(gates_per_block == 128 || gates_per_block == 256 || gates_per_block == 512)) return (int)hipErrorInvalidValue;
   for (uint32_t first = 0; first < count; first += KS_CHUNK) {
     const uint32_t cnt = std::min(KS_CHUNK, count - first);
-    // Gates per workgroup (gpb, at most gates_per_block; registers let a CU
-    // hold 512 / gpb such workgroups) and coefficient ranges per gate tile
-    // (sp): the pair that minimises the rounds of workgroups the device runs
-    // times the cycles of a round on one SIMD -- 512 matrix-core cycles per
-    // coefficient whatever the tile, plus the workgroups' epilogues (stores,
-    // or atomic adds when the ranges are split); larger tiles on ties (fewer
-    // key reads).
-    uint32_t gpb = gates_per_block, best = 1, rows = 1;
-    double best_cost = -1;
-    for (uint32_t g = gates_per_block; g >= 128; g /= 2)
-      for (uint32_t sp = 1; sp <= 32; sp *= 2) {
-        const uint32_t r = (cnt + g - 1) / g;
-        const double rounds = std::ceil((double)r * KS_TILES * sp / (cus * (512 / g)));
-        const double cost = rounds * ((double)(RING_N / sp) * 512.0 + (sp > 1 ? 8192.0 : 4096.0));
-        if (best_cost < 0 || cost < best_cost) {
-          gpb = g;
-          best = sp;
-          rows = r;
-          best_cost = cost;
+    // Gates per workgroup (gpb: 256 or 128, at most gates_per_block; registers
+    // let a CU hold 512 / gpb such workgroups) and coefficient ranges per gate
+    // tile (sp): the pair that minimises the rounds of workgroups the device
+    // runs times the cycles of a round on one SIMD -- 384 matrix-core cycles
+    // per coefficient for either tile, a quarter more for the smaller one,
+    // whose workgroups read the key twice as often (8,197 gates: 607 us with
+    // 256, 766 with 128; 1,024: 112 and 111) -- plus the workgroups' epilogues
+    // (stores, or atomic adds when the ranges are split).  512 gates per
+    // workgroup leave one wavefront per SIMD, whose load waits nothing fills
+    // (682 and 158 us).  Up to 64 gates the key's bytes are what counts: the
+    // wavefronts of a workgroup then share the gates and split the key, so
+    // that each byte is read by one of them.
+    uint32_t gpb = 128, best = 1, rows = 1;
+    const bool split = cnt <= 64;
+    if (split) {
+      gpb = cnt <= 32 ? 32 : 64;
+      best = 32;
+    } else {
+      double best_cost = -1;
+      for (uint32_t g = std::min(gates_per_block, 256u); g >= 128; g /= 2)
+        for (uint32_t sp = 1; sp <= 32; sp *= 2) {
+          const uint32_t r = (cnt + g - 1) / g;
+          const double rounds = std::ceil((double)r * KS_TILES * sp / (cus * (512 / g)));
+          const double cost = rounds * ((double)(RING_N / sp) * (g == 256 ? 384.0 : 480.0) + (sp > 1 ? 8192.0 : 4096.0));
+          if (best_cost < 0 || cost < best_cost) {
+            gpb = g;
+            best = sp;
+            rows = r;
+            best_cost = cost;
+          }
         }
-      }
-    const KsItem* it = items + first;
-    const size_t prep = (size_t)cnt * (RING_N / 4);
-    hipLaunchKernelGGL(ks_prep_kernel, dim3((uint32_t)std::min<size_t>((prep + 255) / 256, 8192)), dim3(256), 0,
-                       S(stream), it, cnt, reinterpret_cast<uint2*>(dig), best > 1 ? 1 : 0);
+    }
+    hipLaunchKernelGGL(ks_prep_kernel, dim3((cnt + PREP_G - 1) / PREP_G, KS_GROUPS / PREP_Q), dim3(256), 0, S(stream),
+                       src, first, cnt, reinterpret_cast<uint2*>(dig), best > 1 ? 1 : 0);
     const dim3 grid(KS_TILES, rows, best);
-    const uint32_t ipb = RING_N / best;
+    const uint32_t per = KS_GROUPS / best;
     const uint4* k = reinterpret_cast<const uint4*>(ksk);
     switch (gpb) {
-      case 128: hipLaunchKernelGGL(ks_mfma_kernel<1>, grid, dim3(256), 0, S(stream), it, cnt, dig, k, ipb); break;
-      case 256: hipLaunchKernelGGL(ks_mfma_kernel<2>, grid, dim3(256), 0, S(stream), it, cnt, dig, k, ipb); break;
-      default: hipLaunchKernelGGL(ks_mfma_kernel<4>, grid, dim3(256), 0, S(stream), it, cnt, dig, k, ipb); break;
+      case 32: hipLaunchKernelGGL((ks_mfma_kernel<1, true>), grid, dim3(256), 0, S(stream), src, first, cnt, dig, k, per); break;
+      case 64: hipLaunchKernelGGL((ks_mfma_kernel<2, true>), grid, dim3(256), 0, S(stream), src, first, cnt, dig, k, per); break;
+      case 128: hipLaunchKernelGGL((ks_mfma_kernel<1, false>), grid, dim3(256), 0, S(stream), src, first, cnt, dig, k, per); break;
+      default: hipLaunchKernelGGL((ks_mfma_kernel<2, false>), grid, dim3(256), 0, S(stream), src, first, cnt, dig, k, per); break;
     }
     const int e = (int)hipGetLastError();
     if (e != 0) return e;
@@ -1311,14 +1367,6 @@ int launch_make_br_items(BrItem* items, uint32_t count, const uint32_t* a, const
   if (count == 0) return 0;
   hipLaunchKernelGGL(make_br_items_kernel, dim3((count + 255) / 256), dim3(256), 0, S(stream), items, count, a, b, ca,
                      cb, cst, mu, out, bk);
-  return (int)hipGetLastError();
-}
-
-int launch_make_ks_items(KsItem* items, uint32_t count, const uint32_t* u1, const uint32_t* u2, uint32_t cst,
-                         uint32_t* out, const uint32_t* ksk, void* stream) {
-  if (count == 0) return 0;
-  hipLaunchKernelGGL(make_ks_items_kernel, dim3((count + 255) / 256), dim3(256), 0, S(stream), items, count, u1, u2,
-                     cst, out, ksk);
   return (int)hipGetLastError();
 }
 

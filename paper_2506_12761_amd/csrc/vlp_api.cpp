@@ -189,6 +189,8 @@ void mark_end(vlp_ctx* ctx, int id, int kind, uint64_t items);
 // except that 4 to 5 per CU run as 4 and 1 (10.3 ms) and 5 to 6 as 4 and 2
 // (11.9 ms); splitting the others gains nothing (2 as 1 and 1: 5.5 ms; 3 as 2
 // and 1: 7.2 ms, within a box's spread of 7.5; 7 as 4, 2 and 1: 14.7 ms).
+KsSource ks_array(const KsItem* items) { return KsSource{items, {}}; }
+
 struct BrRound {
   uint32_t waves, rot_per_block, rotations;
 };
@@ -219,11 +221,11 @@ int timed_br(vlp_ctx* ctx, const BrItem* items, uint32_t count) {
   return 0;
 }
 
-int timed_ks(vlp_ctx* ctx, const KsItem* items, uint32_t count, const uint32_t* ksk, uint32_t* dig) {
+int timed_ks(vlp_ctx* ctx, const KsSource& src, uint32_t count, const uint32_t* ksk, uint32_t* dig) {
   if (count == 0) return 0;
   const int m = mark_begin(ctx);
   const int e =
-      launch_ks_group(items, count, ksk, dig, ctx->tune.ks_gates_per_block, (uint32_t)ctx->num_cus, ctx->stream);
+      launch_ks_group(src, count, ksk, dig, ctx->tune.ks_gates_per_block, (uint32_t)ctx->num_cus, ctx->stream);
   mark_end(ctx, m, 1, count);
   return e;
 }
@@ -487,13 +489,10 @@ extern "C" vlp_status vlp_keyswitch(vlp_ctx* ctx, const vlp_keyset* ks, const ui
   if (!ks || ks->ctx != ctx || !in_dev || !out_dev) return fail(ctx, VLP_EINVAL, "null or foreign argument");
   if (B > (1u << 26)) return fail(ctx, VLP_EINVAL, "B too large");
   if (ranges_overlap(in_dev, B * CT_N * 4, out_dev, B * CT_n * 4)) return fail(ctx, VLP_EINVAL, "in and out overlap");
-  const size_t item_bytes = (B * sizeof(KsItem) + 255) & ~(size_t)255;
-  vlp_status st = ensure_scratch(ctx, item_bytes + ks_digit_bytes(B));
+  vlp_status st = ensure_scratch(ctx, ks_digit_bytes(B));
   if (st != VLP_OK) return st;
-  KsItem* items = (KsItem*)ctx->scratch;
-  uint32_t* dig = (uint32_t*)((char*)ctx->scratch + item_bytes);
-  LAUNCHCHECK(ctx, launch_make_ks_items(items, (uint32_t)B, in_dev, nullptr, 0, out_dev, ks->ksk, ctx->stream));
-  LAUNCHCHECK(ctx, timed_ks(ctx, items, (uint32_t)B, ks->ksk, dig));
+  const KsSource src{nullptr, KsItem{in_dev, nullptr, out_dev, ks->ksk, 0, 0}};
+  LAUNCHCHECK(ctx, timed_ks(ctx, src, (uint32_t)B, ks->ksk, (uint32_t*)ctx->scratch));
   return VLP_OK;
 }
 
@@ -516,11 +515,11 @@ vlp_status gate_args(vlp_ctx* ctx, const vlp_keyset* ks, vlp_gate_op op, const u
 }
 
 // Bytes of scratch a bootstrapped gate call over B gates lays out from `base`:
-// sample-extracted outputs (one or two per gate), then the blind-rotation and
-// key-switching items, then the key-switching digits.
+// sample-extracted outputs (one or two per gate), then the blind-rotation
+// items, then the key-switching digits.
 constexpr size_t gate_scratch_bytes(vlp_gate_op op, size_t B) {
   return (((op == VLP_MUX ? 2 * B : B) * CT_N * 4 + 255) & ~(size_t)255) + (op == VLP_MUX ? 2 * B : B) * sizeof(BrItem) +
-         B * sizeof(KsItem) + ks_digit_bytes(B);
+         ks_digit_bytes(B);
 }
 static_assert(gate_scratch_bytes(VLP_MUX, NOALLOC_MAX_GATES) <= NOALLOC_BYTES, "fixed scratch too small");
 
@@ -532,8 +531,7 @@ vlp_status gate_run(vlp_ctx* ctx, const vlp_keyset* ks, vlp_gate_op op, const ui
   const size_t ext_bytes = (units * CT_N * 4 + 255) & ~(size_t)255;
   uint32_t* ext = (uint32_t*)base;
   BrItem* bri = (BrItem*)((char*)base + ext_bytes);
-  KsItem* ksi = (KsItem*)((char*)bri + units * sizeof(BrItem));
-  uint32_t* dig = (uint32_t*)((char*)ksi + B * sizeof(KsItem));
+  uint32_t* dig = (uint32_t*)((char*)bri + units * sizeof(BrItem));
   int32_t ca, cb;
   uint32_t cst;
   gate_coeffs((uint8_t)op, &ca, &cb, &cst);
@@ -541,13 +539,11 @@ vlp_status gate_run(vlp_ctx* ctx, const vlp_keyset* ks, vlp_gate_op op, const ui
   if (op == VLP_MUX)
     LAUNCHCHECK(ctx, launch_make_br_items(bri + B, (uint32_t)B, a_dev, c_dev, -1, 1, 0u - MU, MU, ext + B * CT_N,
                                           ks->bk, ctx->stream));
+  const KsItem k{ext, op == VLP_MUX ? ext + B * CT_N : nullptr, out_dev, ks->ksk, op == VLP_MUX ? MU : 0u, 0};
   const bool prof = ctx->prof;
   ctx->prof = prof && timed;
   int e = timed_br(ctx, bri, (uint32_t)units);
-  if (e == 0)
-    e = launch_make_ks_items(ksi, (uint32_t)B, ext, op == VLP_MUX ? ext + B * CT_N : nullptr, op == VLP_MUX ? MU : 0u,
-                             out_dev, ks->ksk, ctx->stream);
-  if (e == 0) e = timed_ks(ctx, ksi, (uint32_t)B, ks->ksk, dig);
+  if (e == 0) e = timed_ks(ctx, KsSource{nullptr, k}, (uint32_t)B, ks->ksk, dig);
   ctx->prof = prof;
   if (e != 0) return fail(ctx, VLP_EHIP, "gate launch: %s", hipGetErrorString((hipError_t)e));
   return VLP_OK;
@@ -996,7 +992,7 @@ extern "C" vlp_status vlp_program_destroy(vlp_program* prog) {
 static vlp_status run_level(vlp_ctx* ctx, vlp_program* prog, uint32_t L) {
   const Level& lv = prog->levels[L];
   LAUNCHCHECK(ctx, timed_br(ctx, prog->br_items + lv.br_first, lv.br_count));
-  LAUNCHCHECK(ctx, timed_ks(ctx, prog->ks_items + lv.ks_first, lv.ks_count, prog->ks->ksk, prog->dig_buf));
+  LAUNCHCHECK(ctx, timed_ks(ctx, ks_array(prog->ks_items + lv.ks_first), lv.ks_count, prog->ks->ksk, prog->dig_buf));
   return VLP_OK;
 }
 
@@ -1047,7 +1043,7 @@ extern "C" vlp_status vlp_step(vlp_ctx* ctx, vlp_program* const* progs, size_t n
       vlp_program* pr = progs[p];
       if (pr->next_level >= pr->levels.size()) continue;
       LAUNCHCHECK(ctx,
-                  timed_ks(ctx, ksi + ks_groups[gi].first, (uint32_t)ks_groups[gi].second, pr->ks->ksk, pr->dig_buf));
+                  timed_ks(ctx, ks_array(ksi + ks_groups[gi].first), (uint32_t)ks_groups[gi].second, pr->ks->ksk, pr->dig_buf));
       gi++;
     }
   }

@@ -75,7 +75,7 @@ class Executor:
         pass
 
 
-KEYSET_BYTES = 92905472 + 83886080  # transformed bootstrapping key + key-switching byte planes
+KEYSET_BYTES = 92905472 + 62914560  # transformed bootstrapping key + key-switching byte planes
 
 
 class GpuExecutor(Executor):
