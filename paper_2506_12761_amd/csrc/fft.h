@@ -13,10 +13,10 @@
 // Why the results are exact integers.  A CMux adds, per output word, the
 // negacyclic products of six digit polynomials (|d| <= 64) with key
 // polynomials.  Each key word k (taken signed, |k| <= 2^31) is split as
-// k = 20 hi + lo, lo in [-10, 9]; three real products per coefficient are
+// k = 16 hi + lo, lo in [-8, 7]; three real products per coefficient are
 // computed: hi of output A, hi of output B, and lo of both outputs packed as
-// lo_A + 2^23 lo_B (|sum over lo| <= 6*1024*64*10 < 2^22, so the two parts
-// separate).  Largest key values: |hi| <= 2^26.68, packed < 2^26.33.  With
+// lo_A + 2^23 lo_B (|sum over lo| <= 6*1024*64*8 < 2^22, so the two parts
+// separate).  Largest key values: |hi| <= 2^27, packed < 2^26.01.  With
 // u = 2^-53 and S = sum over the six rows of ||d||_2 ||k||_2
 // <= 6 * (32*64) * (32 max|k|) = 2^18.585 max|k|, the worst-case error of a
 // coefficient is at most S times the sum of the relative errors along the way:
@@ -30,8 +30,10 @@
 //             reaches a coefficient through that stage's elements, which
 //             cover disjoint groups of the 512 values: (1/512) sum |value|
 //             <= S bounds it for every stage.
-// Together 77.8 u S: 0.367 for hi and 0.29 for the packed part, below the 1/2
-// that rounding to the nearest integer allows, for every key and input.
+// Together 77.8 u S: 0.456 for hi and 0.23 for the packed part, below the 1/2
+// that rounding to the nearest integer allows, for every key and input.  (With
+// one channel per output, unsplit, the bound is 7.3: not exact for every
+// input.)
 #pragma once
 #include <stdint.h>
 
@@ -40,19 +42,20 @@
 namespace vlp {
 
 constexpr int FFT_N = 512;         // complex points
-constexpr int KEY_RADIX = 20;      // k = 20 hi + lo
+constexpr int KEY_SHIFT = 4;       // k = 16 hi + lo
 constexpr int LO_SHIFT = 23;       // lo_A + 2^23 lo_B
 constexpr int FFT_CHANNELS = 3;    // hi_A, hi_B, packed lo
 
 // The bounds above: 77.8 u S below 1/2 for both kinds of channel, and the two
 // packed sums apart.
-constexpr double MAX_HI = (2147483648.0 + KEY_RADIX / 2) / KEY_RADIX;
-constexpr double MAX_LO = (KEY_RADIX / 2) * (1.0 + (double)(1 << LO_SHIFT));
+constexpr double MAX_LO_WORD = 1 << (KEY_SHIFT - 1);
+constexpr double MAX_HI = (2147483648.0 + MAX_LO_WORD) / (1 << KEY_SHIFT);
+constexpr double MAX_LO = MAX_LO_WORD * (1.0 + (double)(1 << LO_SHIFT));
 constexpr double ROW_NORMS = 6.0 * (32 * 64) * 32;  // S / max|k|
 constexpr double UNIT_ROUNDOFF = 1.0 / 9007199254740992.0;
-static_assert(77.8 * UNIT_ROUNDOFF * ROW_NORMS * MAX_HI < 0.4 && 77.8 * UNIT_ROUNDOFF * ROW_NORMS * MAX_LO < 0.4,
+static_assert(77.8 * UNIT_ROUNDOFF * ROW_NORMS * MAX_HI < 0.46 && 77.8 * UNIT_ROUNDOFF * ROW_NORMS * MAX_LO < 0.46,
               "rounding to the nearest integer is exact");
-static_assert(6 * 1024 * 64 * (KEY_RADIX / 2) < (1 << (LO_SHIFT - 1)), "the packed sums separate");
+static_assert(6 * 1024 * 64 * MAX_LO_WORD < (1 << (LO_SHIFT - 1)), "the packed sums separate");
 
 struct Cplx {
   double r, i;

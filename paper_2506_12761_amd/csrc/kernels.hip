@@ -57,11 +57,8 @@ __global__ __launch_bounds__(256) void bk_transform_kernel(const uint32_t* __res
   const uint32_t row = blockIdx.x / FFT_CHANNELS, ch = blockIdx.x % FFT_CHANNELS;  // row = i * 6 + r
   const uint32_t* a = bk_coeff + (size_t)row * 2 * RING_N;
   auto word = [&](const uint32_t* p, uint32_t j, double* hi) -> double {  // lo; *hi
-    const int32_t k = (int32_t)p[j];
-    int32_t lo = k % KEY_RADIX;  // truncated remainder in (-20, 20), to [-10, 9]
-    if (lo >= KEY_RADIX / 2) lo -= KEY_RADIX;
-    if (lo < -KEY_RADIX / 2) lo += KEY_RADIX;
-    *hi = (double)(((int64_t)k - lo) / KEY_RADIX);
+    const int32_t k = (int32_t)p[j], lo = (int32_t)((uint32_t)k << (32 - KEY_SHIFT)) >> (32 - KEY_SHIFT);
+    *hi = (double)(((int64_t)k - lo) >> KEY_SHIFT);
     return (double)lo;
   };
   auto value = [&](uint32_t j) -> double {
@@ -158,12 +155,10 @@ __global__ __launch_bounds__(256) void ksk_relayout_kernel(const uint32_t* __res
 // filled by another wavefront (1,024: 7.86 ms; every 8 7.60, every 16 7.50).
 constexpr int steps_per_barrier(int rot) { return rot == 8 ? 1 : 16; }
 
-constexpr uint32_t DEC_OFFSET = (1u << 31) + (1u << 24) + (1u << 17) + (1u << 10);
-// Balanced digit l of D (with DEC_OFFSET added) is its 7-bit field minus 64,
-// i.e. the field with bit 6 flipped read as a signed 7-bit number: flipping
-// those bits once per coefficient lets one signed bit-field extract give
-// each digit.
-constexpr uint32_t DIGIT_FLIP = (1u << 31) | (1u << 24) | (1u << 17);
+// Rounding and the halves of the two lower digits: the top digit of a
+// difference plus this offset is its top field read as a signed number, and
+// the lower ones their fields minus 64, i.e. with bit 6 flipped, likewise.
+constexpr uint32_t DEC_OFFSET = (1u << 24) + (1u << 17) + (1u << 10);
 
 // Accumulator polynomial in LDS: rows of 32 coefficients behind one row that
 // holds the negated last row, so that coefficient j - ab of a lane that falls
@@ -257,9 +252,6 @@ __global__ __launch_bounds__(64 * ROT) __attribute__((amdgpu_waves_per_eu(2))) v
     }
   }
   const double magic = 6755399441055744.0;  // 1.5 * 2^52: the sum's low words are the nearest integer
-  const double magic_lo = magic + (c ? (double)(1 << (LO_SHIFT - 1)) : 0.0);
-  uint32_t lo_shift = c ? LO_SHIFT : 0;
-  asm("" : "+v"(lo_shift));  // one funnel shift by a register, not a shift and a select
   const int unit = wave * (int)((gridDim.x + NUM_XCD - 1) / NUM_XCD) + (int)(blockIdx.x / NUM_XCD);
   uint32_t own[32];  // this lane's accumulator coefficients
 #pragma unroll
@@ -287,7 +279,7 @@ __global__ __launch_bounds__(64 * ROT) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
       for (int R = 0; R < 32; ++R) {
         const uint32_t mask = 0u - (uint32_t)(((R - abh) >> 5) & 1);
-        D[R] = ((w[R] ^ mask) + ((DEC_OFFSET - mask) - own[R])) ^ DIGIT_FLIP;
+        D[R] = (w[R] ^ mask) + ((DEC_OFFSET - mask) - own[R]);
       }
     }
     Cplx s[FFT_CHANNELS][8];
@@ -306,7 +298,7 @@ __global__ __launch_bounds__(64 * ROT) __attribute__((amdgpu_waves_per_eu(2))) v
         if constexpr (first) {
           z[q].r = (double)((int)D[q] >> 25);
           z[q].i = (double)((int)D[16 + q] >> 25);
-          P[q] = ((D[q] >> 9) & 0xFFFFu) | ((D[16 + q] << 7) & 0xFFFF0000u);
+          P[q] = (((D[q] >> 9) & 0xFFFFu) | ((D[16 + q] << 7) & 0xFFFF0000u)) ^ 0x81008100u;
         } else {
           z[q].r = (double)(int)__builtin_amdgcn_sbfe(P[q], shift, (unsigned)BG_BIT);
           z[q].i = (double)(int)__builtin_amdgcn_sbfe(P[q], shift + 16, (unsigned)BG_BIT);
@@ -395,7 +387,7 @@ __global__ __launch_bounds__(64 * ROT) __attribute__((amdgpu_waves_per_eu(2))) v
     inv_stages654(s[0], ta);
     inv_stages654(s[1], ta);
     __builtin_amdgcn_sched_barrier(0);
-    Cplx h[16], z[16];
+    Cplx h[16];
     wave_lds_sync();
 #pragma unroll
     for (int m = 0; m < 8; ++m) xr[4 * m] = s[0][m].r;
@@ -417,19 +409,23 @@ __global__ __launch_bounds__(64 * ROT) __attribute__((amdgpu_waves_per_eu(2))) v
     swap_23(s[2]);
     inv_stages654(s[2], ta);
     __builtin_amdgcn_sched_barrier(0);
-    const double* xp = s_x[wave] + l;  // the packed channel: both halves read the same values
+    // The packed channel over all 64 lanes (layout 4).
+    double* pw = xr;
+    const double* pr = s_x[wave] + XROW * 8 * c + l;
+    Cplx z[8];
     wave_lds_sync();
 #pragma unroll
-    for (int m = 0; m < 8; ++m) xr[4 * m] = s[2][m].r;
+    for (int m = 0; m < 8; ++m) {
+      pw[4 * m] = s[2][m].r;
+      pw[XPOLY + 4 * m] = s[2][m].i;
+    }
     wave_lds_sync();
+    const TwC tc = load_twc(tw);
 #pragma unroll
-    for (int q = 0; q < 16; ++q) z[q].r = xp[XROW * q];
-    wave_lds_sync();
-#pragma unroll
-    for (int m = 0; m < 8; ++m) xr[4 * m] = s[2][m].i;
-    wave_lds_sync();
-#pragma unroll
-    for (int q = 0; q < 16; ++q) z[q].i = xp[XROW * q];
+    for (int m = 0; m < 8; ++m) {
+      z[m].r = pr[XROW * m];
+      z[m].i = pr[XPOLY + XROW * m];
+    }
 #pragma unroll
     for (int R = 0; R < 32; ++R) own[R] = acc[32 * R];
     __builtin_amdgcn_sched_barrier(0);
@@ -444,20 +440,23 @@ __global__ __launch_bounds__(64 * ROT) __attribute__((amdgpu_waves_per_eu(2))) v
       hi[16 + q] = (uint32_t)__builtin_bit_cast(uint64_t, h[q].i + magic);
     }
     __builtin_amdgcn_sched_barrier(0);
-    inv_stage1<3>(z);
-    inv_stage1<2>(z);
-    inv_stage1<1>(z);
-    inv_stage1<0>(z);
+    inv_stages3210(z, tc);
+    // Register m = (i8 i6 i5), lane (i7 | l): the integers of both outputs for
+    // rows R (i7 = 0) and R + 4 (i7 = 1); a lane swap turns lane bit 5 from i7
+    // into the output, as in hi.
 #pragma unroll
-    for (int R = 0; R < 32; ++R) {
-      const uint64_t w = __builtin_bit_cast(uint64_t, (R < 16 ? z[R & 15].r : z[R & 15].i) + magic_lo);
-      const uint32_t f = __builtin_amdgcn_alignbit((uint32_t)(w >> 32), (uint32_t)w, lo_shift);
-      const int32_t lo = __builtin_amdgcn_sbfe((int)f, 0u, (unsigned)LO_SHIFT);
-      static_assert(KEY_RADIX == 20, "20 h + lo = ((5 h) << 2) + lo in two shift-adds");
-      uint32_t h5 = (hi[R] << 2) + hi[R];
-      asm("" : "+v"(h5));  // not a 32-bit multiply
-      own[R] += (h5 << 2) + (uint32_t)lo;
+    for (int t = 0; t < 16; ++t) {
+      const int m = t & 7, R = 8 * (m >> 2) + 2 * ((m >> 1) & 1) + (m & 1) + 16 * (t >> 3);
+      const double x = t < 8 ? z[m].r : z[m].i;
+      const uint32_t la = __builtin_amdgcn_sbfe((uint32_t)__builtin_bit_cast(uint64_t, x + magic), 0u, (unsigned)LO_SHIFT);
+      const uint64_t wb = __builtin_bit_cast(uint64_t, x + (magic + (double)(1 << (LO_SHIFT - 1))));
+      const uint32_t lb = __builtin_amdgcn_sbfe(
+          __builtin_amdgcn_alignbit((uint32_t)(wb >> 32), (uint32_t)wb, LO_SHIFT), 0u, (unsigned)LO_SHIFT);
+      const auto lo = __builtin_amdgcn_permlane32_swap(la, lb, false, false);
+      own[R] += (hi[R] << KEY_SHIFT) + lo[0];
+      own[R + 4] += (hi[R + 4] << KEY_SHIFT) + lo[1];
       acc[32 * R] = own[R];
+      acc[32 * (R + 4)] = own[R + 4];
     }
     acc[-32] = 0u - own[31];
     asm volatile("" ::"v"(touched));
@@ -693,10 +692,8 @@ __global__ __launch_bounds__(192 * BR3_ROT) __attribute__((amdgpu_waves_per_eu(2
       for (int t = 0; t < 16; ++t) {
         const int m = t & 7, R = 8 * (m >> 2) + 2 * ((m >> 1) & 1) + (m & 1) + 16 * (t >> 3);
         old[t] = ap[32 * R];
-        uint32_t x = (uint32_t)__builtin_bit_cast(uint64_t, (t < 8 ? h[m].r : h[m].i) + magic);
-        uint32_t h5 = (x << 2) + x;
-        asm("" : "+v"(h5));
-        hi[t] = old[t] + (h5 << 2);
+        const uint32_t x = (uint32_t)__builtin_bit_cast(uint64_t, (t < 8 ? h[m].r : h[m].i) + magic);
+        hi[t] = old[t] + (x << KEY_SHIFT);
       }
     }
     __syncthreads();
@@ -953,9 +950,7 @@ __global__ __launch_bounds__(384) __attribute__((amdgpu_waves_per_eu(2))) void b
       for (int t = 0; t < 8; ++t) {
         const int J = 256 * ((t >> 1) & 1) + 64 * (t & 1) + 512 * (t >> 2);
         const uint32_t h = (uint32_t)__builtin_bit_cast(uint64_t, (t < 4 ? o[t & 3].r : o[t & 3].i) + magic);
-        uint32_t h5 = (h << 2) + h;
-        asm("" : "+v"(h5));
-        x[t] = ap[J] + (h5 << 2);
+        x[t] = ap[J] + (h << KEY_SHIFT);
       }
     }
     __syncthreads();
