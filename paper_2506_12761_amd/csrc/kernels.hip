@@ -135,18 +135,21 @@ __global__ __launch_bounds__(256) void ksk_relayout_kernel(const uint32_t* __res
 // Blind rotation + sample extraction, one wavefront per rotation
 // (br1_kernel): the whole CMux in one wavefront, so its steps need no
 // workgroup barrier.  Bound: double-precision FMA issue.  Per step and
-// wavefront about 3,750 VALU instructions (288 of them lane swaps that take
+// wavefront about 3,600 VALU instructions (320 of them lane swaps that take
 // two issue slots): 6 forward and 3 inverse 512-point transforms (216 and 288
-// FMAs or adds per lane), 576 product FMAs, 330 for rotation and digits, 224
+// FMAs or adds per lane), 576 product FMAs, 370 for rotation and digits, 180
 // for rounding and recombination.  256 VGPRs, two wavefronts per SIMD, 8
 // rotations per CU.
-// Beside the VALU (16.2k of 23k clocks a step and wavefront at 8 rotations
-// per CU) the step moves 147 KB of key through the vector L1 (64 B/clk) and
-// about 2k clocks of LDS traffic; both are kept in flight behind arithmetic
-// (eight key loads always outstanding, the exchange's real parts under way
-// while the imaginary ones are computed).
+// Beside the VALU (15.6k of 22.5k clocks a step and wavefront at 8 rotations
+// per CU) the step moves 147 KB of key through the vector L1 (64 B/clk; without
+// the loads a round takes 14% less, whether they hit the L1 or not) and about
+// 1.5k clocks of LDS traffic (9% less without the exchanges); both are kept in
+// flight behind arithmetic (eight key loads always outstanding, the exchange's
+// real parts under way while the imaginary ones are computed).
 // Measured (rotations only): 2,048 in 12.0 ms (171k/s; the two-prime NTT
-// kernel it replaces: 21.7 ms, 94k/s), 1,024 at 4 per CU in 7.5 ms (10.9 ms).
+// kernel it replaces: 21.7 ms, 94k/s), 1,024 at 4 per CU in 7.1 ms (10.9 ms;
+// 7.6 with at most 256 registers per wavefront, which 8 per CU need and which
+// spill 20).
 // ---------------------------------------------------------------------------
 // The wavefronts of a workgroup read the same key: a barrier every few steps
 // keeps them close enough to share it in the L1 and L2.  With 8 per CU every
@@ -203,14 +206,14 @@ __device__ __forceinline__ uint32_t key_touch(__amdgpu_buffer_rsrc_t key, int la
                                               use ? (step * STEP_BATCHES + batch) * 8192 : 0, 0);
 }
 
-// s += a * v for one channel; NEXT: replaces v by the batch at offset off.
-template <bool NEXT>
+// s += a * v for one channel (FIRST: s = a * v); NEXT: replaces v by the batch at offset off.
+template <bool FIRST, bool NEXT>
 __device__ __forceinline__ void key_products(Cplx (&s)[8], const Cplx (&a)[8], double2 (&v)[8],
                                              __amdgpu_buffer_rsrc_t key, int lane16, int off) {
 #pragma unroll
   for (int m = 0; m < 8; ++m) {
-    s[m].r = __builtin_fma(a[m].r, v[m].x, s[m].r);
-    s[m].i = __builtin_fma(a[m].r, v[m].y, s[m].i);
+    s[m].r = FIRST ? a[m].r * v[m].x : __builtin_fma(a[m].r, v[m].x, s[m].r);
+    s[m].i = FIRST ? a[m].r * v[m].y : __builtin_fma(a[m].r, v[m].y, s[m].i);
     s[m].r = __builtin_fma(-a[m].i, v[m].y, s[m].r);
     s[m].i = __builtin_fma(a[m].i, v[m].x, s[m].i);
     if (NEXT) key_load(v, key, lane16, off, m);
@@ -219,7 +222,7 @@ __device__ __forceinline__ void key_products(Cplx (&s)[8], const Cplx (&a)[8], d
 }
 
 template <int ROT>
-__global__ __launch_bounds__(64 * ROT) __attribute__((amdgpu_waves_per_eu(2))) void br1_kernel(
+__global__ __launch_bounds__(64 * ROT) __attribute__((amdgpu_waves_per_eu(ROT > 4 ? 2 : 1))) void br1_kernel(
     const BrItem* __restrict__ items, uint32_t count, const double2* __restrict__ lane_tw) {
   __shared__ uint32_t s_acc[ROT][2 * ACC_WORDS];
   __shared__ double s_x[ROT][2 * XPOLY];
@@ -283,10 +286,6 @@ __global__ __launch_bounds__(64 * ROT) __attribute__((amdgpu_waves_per_eu(2))) v
       }
     }
     Cplx s[FFT_CHANNELS][8];
-#pragma unroll
-    for (int ch = 0; ch < FFT_CHANNELS; ++ch)
-#pragma unroll
-      for (int m = 0; m < 8; ++m) s[ch][m] = {0.0, 0.0};
     // The second and third digits of two coefficients share a word, which
     // halves the registers they occupy while the first is worked on.
     uint32_t P[16];
@@ -349,23 +348,23 @@ __global__ __launch_bounds__(64 * ROT) __attribute__((amdgpu_waves_per_eu(2))) v
       swap_23(a);
       fwd_stages78(a, tb);
       __builtin_amdgcn_sched_barrier(0);
-      key_products<true>(s[0], a, v, key, lane16, off + 1 * 8192);
+      key_products<first, true>(s[0], a, v, key, lane16, off + 1 * 8192);
       fwd_stages456(b, ta);
       __builtin_amdgcn_sched_barrier(0);
-      key_products<true>(s[1], a, v, key, lane16, off + 2 * 8192);
+      key_products<first, true>(s[1], a, v, key, lane16, off + 2 * 8192);
       swap_23(b);
       __builtin_amdgcn_sched_barrier(0);
-      key_products<true>(s[2], a, v, key, lane16, off + 3 * 8192);
+      key_products<first, true>(s[2], a, v, key, lane16, off + 3 * 8192);
       double2 w[8];
 #pragma unroll
       for (int m = 0; m < 8; ++m) key_load(w, key, lane16, off + 4 * 8192, m);
       __builtin_amdgcn_sched_barrier(0);
       fwd_stages78(b, tb);
       __builtin_amdgcn_sched_barrier(0);
-      key_products<true>(s[0], b, v, key, lane16, off + 5 * 8192);
-      key_products<false>(s[1], b, w, key, lane16, 0);
+      key_products<false, true>(s[0], b, v, key, lane16, off + 5 * 8192);
+      key_products<false, false>(s[1], b, w, key, lane16, 0);
       off += 6 * 8192;
-      key_products<true>(s[2], b, v, key, lane16, off);
+      key_products<false, true>(s[2], b, v, key, lane16, off);
     };
     digit(std::true_type(), 0);
 #pragma unroll 1
