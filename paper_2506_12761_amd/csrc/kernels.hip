@@ -140,12 +140,12 @@ __global__ __launch_bounds__(256) void ksk_relayout_kernel(const uint32_t* __res
 // FMAs or adds per lane), 576 product FMAs, 370 for rotation and digits, 180
 // for rounding and recombination.  256 VGPRs, two wavefronts per SIMD, 8
 // rotations per CU.
-// Beside the VALU (15.6k of 22.5k clocks a step and wavefront at 8 rotations
-// per CU) the step moves 147 KB of key through the vector L1 (64 B/clk; without
-// the loads a round takes 14% less, whether they hit the L1 or not) and about
-// 1.5k clocks of LDS traffic (9% less without the exchanges); both are kept in
-// flight behind arithmetic (eight key loads always outstanding, the exchange's
-// real parts under way while the imaginary ones are computed).
+// The VALU issues for 15.7k of the 22.5k clocks of a step and wavefront at 8
+// rotations per CU (counters: 70% busy).  Beside it the step moves 147 KB of
+// key through the vector L1 (64 B/clk; a build without these loads takes 10.7
+// instead of 12.0 ms for 2,048) and exchanges its transforms through LDS; both
+// are kept in flight behind arithmetic (eight key loads always outstanding, the
+// exchange's real parts under way while the imaginary ones are computed).
 // Measured (rotations only): 2,048 in 12.0 ms (171k/s; the two-prime NTT
 // kernel it replaces: 21.7 ms, 94k/s), 1,024 at 4 per CU in 7.1 ms (10.9 ms;
 // 7.6 with at most 256 registers per wavefront, which 8 per CU need and which
@@ -153,9 +153,9 @@ __global__ __launch_bounds__(256) void ksk_relayout_kernel(const uint32_t* __res
 // ---------------------------------------------------------------------------
 // The wavefronts of a workgroup read the same key: a barrier every few steps
 // keeps them close enough to share it in the L1 and L2.  With 8 per CU every
-// step is best (2,048 rotations back to back: 12.20 ms; every 8 steps 12.38,
-// every 16 12.45); with 4, one per SIMD, the stalls of a barrier are not
-// filled by another wavefront (1,024: 7.86 ms; every 8 7.60, every 16 7.50).
+// step is best (2,048 rotations back to back: 11.99 ms; every 8 steps 12.14,
+// every 16 12.22); with 4, one per SIMD, the stalls of a barrier are not
+// filled by another wavefront (1,024: 7.45 ms; every 8 7.16, every 16 7.12).
 constexpr int steps_per_barrier(int rot) { return rot == 8 ? 1 : 16; }
 
 // Rounding and the halves of the two lower digits: the top digit of a

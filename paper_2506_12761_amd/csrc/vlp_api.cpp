@@ -186,8 +186,8 @@ void mark_end(vlp_ctx* ctx, int id, int kind, uint64_t items);
 // the measured times of a round: up to 1 per CU 2.8 ms (six wavefronts per
 // rotation), up to 2 4.4 ms (three), up to 4 7.1 ms (one each, one per SIMD),
 // up to 8 12.0 ms (two per SIMD).  So the smallest round that holds the rest,
-// except that 4 to 5 per CU run as 4 and 1 (9.9 ms) and 5 to 6 as 4 and 2
-// (11.5 ms); splitting the others gains nothing (2 as 1 and 1: 5.5 ms; 3 as 2
+// except that 4 to 5 per CU run as 4 and 1 (9.9 ms, the sum of both) and 5 to 6
+// as 4 and 2 (11.5 ms); splitting the others gains nothing (2 as 1 and 1: 5.5 ms; 3 as 2
 // and 1: 7.2 ms; 7 as 4, 2 and 1: 14.3 ms).
 KsSource ks_array(const KsItem* items) { return KsSource{items, {}}; }
 
