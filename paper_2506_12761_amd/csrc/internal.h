@@ -98,7 +98,7 @@ int launch_ksk_relayout(const uint32_t* ksk_in, uint32_t* ksk_out, void* stream)
 // Blind rotations by `waves` (1, 3 or 6) wavefronts each, rot_per_block of
 // them per workgroup (1 wavefront: 1, 2, 4, 8; 3: 2; 6: 1).
 int launch_br(const BrItem* items, uint32_t count, const FftTables* tables, uint32_t waves, uint32_t rot_per_block,
-              void* stream);
+              uint32_t cus, void* stream);
 // ServerEnc over a flat [count][631] array; out == pk runs in place.
 int launch_server_enc(const uint32_t* pk, uint32_t* out, size_t count, const int64_t* vals, const uint8_t* bytes,
                       uint32_t l, void* stream);

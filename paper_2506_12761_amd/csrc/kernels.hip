@@ -206,6 +206,31 @@ __device__ __forceinline__ uint32_t key_touch(__amdgpu_buffer_rsrc_t key, int la
                                               use ? (step * STEP_BATCHES + batch) * 8192 : 0, 0);
 }
 
+// Brings the keys of a round's first and last rotation from HBM into the
+// memory-side cache (256 MiB, two keys), one load per 128-byte line: workgroup
+// part of parts.  A rotation by itself waits for HBM in each of its steps when
+// its key has not been used lately, as it keeps only a step's loads in flight;
+// a workgroup on a CU that a small round leaves idle, which touches lines only,
+// runs well ahead of it.  One rotation with a key from HBM: 3.23 -> 2.79 ms, 300:
+// 4.82 -> 4.42 ms.  With the key there already: 2.77 -> 2.78 and 4.39 -> 4.41 ms.
+// More such workgroups (4, 8, 32 or all idle CUs) gain nothing further.  Loading
+// into the L2 just ahead of use would gain at most 4% more for one rotation and
+// nothing for 37.
+constexpr uint32_t WARM_BLOCKS = 2;
+__device__ __forceinline__ void key_warm(const BrItem* __restrict__ items, uint32_t count, uint32_t part,
+                                         uint32_t parts) {
+  const void* const keys[2] = {items[0].bk, items[count - 1].bk};
+  const uint32_t n = keys[0] == keys[1] ? 1 : 2;
+  for (uint32_t k = 0; k < n; ++k) {
+    const __amdgpu_buffer_rsrc_t key =
+        __builtin_amdgcn_make_buffer_rsrc((void*)keys[k], 0, (int)BK_FFT_BYTES, 0x00027000);
+    for (uint32_t e = part * blockDim.x + threadIdx.x; e < BK_FFT_BYTES / 128; e += parts * blockDim.x) {
+      const uint32_t x = __builtin_amdgcn_raw_buffer_load_b32(key, (int)(e * 128), 0, 0);
+      asm volatile("" ::"v"(x));
+    }
+  }
+}
+
 // s += a * v for one channel (FIRST: s = a * v); NEXT: replaces v by the batch at offset off.
 template <bool FIRST, bool NEXT>
 __device__ __forceinline__ void key_products(Cplx (&s)[8], const Cplx (&a)[8], double2 (&v)[8],
@@ -490,6 +515,14 @@ __global__ __launch_bounds__(192 * BR3_ROT) __attribute__((amdgpu_waves_per_eu(2
     const BrItem* __restrict__ items, uint32_t count, const double2* __restrict__ lane_tw) {
   constexpr int REGION = 2 * XPOLY;  // doubles: one polynomial's values (1,024 doubles), padded for the exchange
   constexpr int REGIONS = 6;
+  const uint32_t blocks = (count + BR3_ROT - 1) / BR3_ROT;
+  if (blockIdx.x >= blocks) {
+    key_warm(items, count, blockIdx.x - blocks, gridDim.x - blocks);
+    return;
+  }
+  // No CU is idle: every workgroup reads its part first (512 rotations: 4.82 ->
+  // 4.40 ms with a key from HBM, 4.38 and 4.36 ms otherwise).
+  if (gridDim.x == blocks) key_warm(items, count, blockIdx.x, blocks);
   __shared__ double s_x[BR3_ROT][REGIONS][REGION];
   __shared__ double2 s_tw[LANE_TW][64];
   __shared__ uint32_t s_acc[BR3_ROT][2][3 * RING_N];
@@ -771,6 +804,10 @@ __global__ __launch_bounds__(384) __attribute__((amdgpu_waves_per_eu(2))) void b
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int j = w >> 1, c = w & 1;         // forward: digit j of polynomial c
   const int hf = w >= 3, ch = w - 3 * hf;  // products and inverse: half hf (i8) of channel ch
+  if (blockIdx.x >= count) {
+    key_warm(items, count, blockIdx.x - count, gridDim.x - count);
+    return;
+  }
   const BrItem I = items[blockIdx.x];
   // Twiddles in registers for the whole rotation.
   const double2* lt = reinterpret_cast<const double2*>(tables->lane) + lane;
@@ -1286,9 +1323,16 @@ int launch_ksk_relayout(const uint32_t* ksk_in, uint32_t* ksk_out, void* stream)
 }
 
 int launch_br(const BrItem* items, uint32_t count, const FftTables* tables, uint32_t waves, uint32_t rot_per_block,
-              void* stream) {
+              uint32_t cus, void* stream) {
   if (count == 0) return 0;
-  const dim3 grid((count + rot_per_block - 1) / rot_per_block), block(64 * waves * rot_per_block);
+  // Workgroups behind the rotations', on the CUs that those leave idle, read the
+  // key ahead (key_warm).  A full round of br6 has none and goes without: its
+  // own workgroups reading ahead would take 2.84 instead of 3.06 ms for 256
+  // rotations with a key from HBM, but 2.81 instead of 2.78 ms otherwise.
+  // br1 reads ahead step by step (key_touch) and gains nothing from it.
+  const uint32_t blocks = (count + rot_per_block - 1) / rot_per_block;
+  const uint32_t ahead = waves > 1 && blocks < cus ? std::min(WARM_BLOCKS, cus - blocks) : 0;
+  const dim3 grid(blocks + ahead), block(64 * waves * rot_per_block);
   const double2* tw = reinterpret_cast<const double2*>(tables->lane);
   switch (waves * 16 + rot_per_block) {
     case 16 + 1: hipLaunchKernelGGL(br1_kernel<1>, grid, block, 0, S(stream), items, count, tw); break;

@@ -213,7 +213,8 @@ int timed_br(vlp_ctx* ctx, const BrItem* items, uint32_t count) {
     const BrRound r = next_round(ctx->tune, (uint32_t)ctx->num_cus, count - first);
     const uint32_t n = std::min(r.rotations, count - first);
     const int m = mark_begin(ctx);
-    const int e = launch_br(items + first, n, ctx->tables, r.waves, r.rot_per_block, ctx->stream);
+    const int e = launch_br(items + first, n, ctx->tables, r.waves, r.rot_per_block, (uint32_t)ctx->num_cus,
+                            ctx->stream);
     mark_end(ctx, m, 0, n);
     if (e != 0) return e;
     first += n;

@@ -25,7 +25,7 @@ def uniform():
         yield vlp, ctx, ctx.load_keys(bk, ksk), keys
 
 
-@pytest.mark.parametrize("per_cu,extra", [(0, 1), (1, 0), (1, 1), (2, 0), (2, 1), (4, 0), (4, 1), (6, 0), (6, 1), (8, 0), (8, 3)])
+@pytest.mark.parametrize("per_cu,extra", [(0, 1), (1, -1), (1, 0), (1, 1), (2, 0), (2, 1), (4, 0), (4, 1), (6, 0), (6, 1), (8, 0), (8, 3)])
 def test_round_boundaries(uniform, per_cu, extra):
     """Batches on both sides of every line of the automatic choice (rotations
     per CU): the last rotation, the first of each round and a sample."""
