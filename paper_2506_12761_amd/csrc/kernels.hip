@@ -151,7 +151,8 @@ __global__ __launch_bounds__(256) void ksk_relayout_kernel(const uint32_t* __res
 // are kept in flight behind arithmetic (eight key loads always outstanding, the
 // exchange's real parts under way while the imaginary ones are computed).
 // Measured (rotations only): 2,048 in 12.0 ms (171k/s; the two-prime NTT
-// kernel it replaces: 21.7 ms, 94k/s), 1,024 at 4 per CU in 7.1 ms (10.9 ms;
+// kernel it replaces: 21.7 ms, 94k/s; 12.0 to 12.5 ms on
+// different cards), 1,024 at 4 per CU in 7.1 ms (10.9 ms;
 // 7.6 with at most 256 registers per wavefront, which 8 per CU need and which
 // spill 20).
 // ---------------------------------------------------------------------------
