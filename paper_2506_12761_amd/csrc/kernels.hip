@@ -637,7 +637,7 @@ __global__ __launch_bounds__(192 * BR3_ROT) __attribute__((amdgpu_waves_per_eu(2
     const int next = i + 1 < LWE_n ? off + 18 * 8192 : off;  // the next step's batches
     auto mul = [&](const Cplx (&x)[8], auto n_t) {
       constexpr int n = decltype(n_t)::value;
-      const int to = n < 5 ? off + order[n + 1] : next + order[0];
+      const int to = (n < 5 ? off : next) + order[(n + 1) % 6];
 #pragma unroll
       for (int m = 0; m < 8; ++m) {
         if constexpr (n % 2 == 0) {
