@@ -213,26 +213,39 @@ __device__ __forceinline__ uint32_t key_touch(__amdgpu_buffer_rsrc_t key, int la
 
 // Brings the keys of a round's first and last rotation from HBM into the
 // memory-side cache (256 MiB, two keys), one load per 128-byte line: workgroup
-// part of parts.  A rotation by itself waits for HBM in each of its steps when
-// its key has not been used lately, as it keeps only a step's loads in flight;
-// a workgroup on a CU that a small round leaves idle, which touches lines only,
-// runs well ahead of it.  One rotation with a key from HBM: 3.23 -> 2.79 ms, 300:
-// 4.82 -> 4.42 ms.  With the key there already: 2.77 -> 2.78 and 4.39 -> 4.41 ms.
-// More such workgroups (4, 8, 32 or all idle CUs) gain nothing further.  Loading
-// into the L2 just ahead of use would gain at most 4% more for one rotation and
-// nothing for 37.
-constexpr uint32_t WARM_BLOCKS = 2;
+// part of parts, WARM_THREADS threads.  A rotation by itself waits for HBM in each
+// of its steps when its key has not been used lately, as it keeps only a step's
+// loads in flight; a workgroup on a CU that a small round leaves idle, which
+// touches lines only, runs well ahead of it.  One rotation with a key from HBM:
+// 3.23 -> 2.79 ms, 300: 4.82 -> 4.42 ms.  With the key there already: 2.77 -> 2.78
+// and 4.39 -> 4.41 ms.  More such workgroups (4, 8, 32 or all idle CUs) gain
+// nothing further.  Loading into the L2 just ahead of use would gain at most 4%
+// more for one rotation and nothing for 37.
+// A launch ends no earlier than its helpers, so a thread keeps WARM_LOADS loads
+// in flight: a helper by itself with two keys then waits less often than the
+// rotations have steps.  With one load at a time it waited 3,780 times: 510
+// rotations with two keys took 4.71 ms (4.53 on another card; now 4.39) where
+// 512, without a helper, take 4.44, and 255 took 2.96 (now 2.88).  The lines of
+// two keys are taken in turn; those of further keys between them are not read.
+constexpr uint32_t WARM_BLOCKS = 2, WARM_THREADS = 384, WARM_LOADS = 8;
+constexpr uint32_t KEY_LINES = BK_FFT_BYTES / 128;
+static_assert(2 * ((KEY_LINES + WARM_THREADS * WARM_LOADS - 1) / (WARM_THREADS * WARM_LOADS)) < LWE_n,
+              "a helper by itself ends before the rotations");
 __device__ __forceinline__ void key_warm(const BrItem* __restrict__ items, uint32_t count, uint32_t part,
                                          uint32_t parts) {
-  const void* const keys[2] = {items[0].bk, items[count - 1].bk};
-  const uint32_t n = keys[0] == keys[1] ? 1 : 2;
-  for (uint32_t k = 0; k < n; ++k) {
-    const __amdgpu_buffer_rsrc_t key =
-        __builtin_amdgcn_make_buffer_rsrc((void*)keys[k], 0, (int)BK_FFT_BYTES, 0x00027000);
-    for (uint32_t e = part * blockDim.x + threadIdx.x; e < BK_FFT_BYTES / 128; e += parts * blockDim.x) {
-      const uint32_t x = __builtin_amdgcn_raw_buffer_load_b32(key, (int)(e * 128), 0, 0);
-      asm volatile("" ::"v"(x));
-    }
+  const void *const first = items[0].bk, *const last = items[count - 1].bk;
+  const uint32_t stride = parts * WARM_THREADS;
+  auto touch = [&](const void* bk, uint32_t e) {  // lines past the key's end are out of the buffer's range: nothing is read
+    const __amdgpu_buffer_rsrc_t key = __builtin_amdgcn_make_buffer_rsrc((void*)bk, 0, (int)BK_FFT_BYTES, 0x00027000);
+    uint32_t x[WARM_LOADS];
+#pragma unroll
+    for (uint32_t u = 0; u < WARM_LOADS; ++u)
+      x[u] = __builtin_amdgcn_raw_buffer_load_b32(key, (int)((e + u * stride) * 128), 0, 0);
+    asm volatile("" ::"v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]));
+  };
+  for (uint32_t e = part * WARM_THREADS + threadIdx.x; e < KEY_LINES; e += WARM_LOADS * stride) {
+    touch(first, e);
+    if (last != first) touch(last, e);
   }
 }
 
@@ -520,6 +533,7 @@ __global__ __launch_bounds__(192 * BR3_ROT) __attribute__((amdgpu_waves_per_eu(2
     const BrItem* __restrict__ items, uint32_t count, const double2* __restrict__ lane_tw) {
   constexpr int REGION = 2 * XPOLY;  // doubles: one polynomial's values (1,024 doubles), padded for the exchange
   constexpr int REGIONS = 6;
+  static_assert(192 * BR3_ROT == WARM_THREADS, "key_warm's workgroup");
   const uint32_t blocks = (count + BR3_ROT - 1) / BR3_ROT;
   if (blockIdx.x >= blocks) {
     key_warm(items, count, blockIdx.x - blocks, gridDim.x - blocks);
@@ -800,7 +814,7 @@ __device__ __forceinline__ void inv_half2(Cplx (&z)[4], const HalfTw& t, int e) 
   bf_inv<false>(z[1], z[3], t.r[e + 1], t.i[e + 1]);
 }
 
-__global__ __launch_bounds__(384) __attribute__((amdgpu_waves_per_eu(2))) void br6_kernel(
+__global__ __launch_bounds__(WARM_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void br6_kernel(
     const BrItem* __restrict__ items, uint32_t count, const FftTables* __restrict__ tables) {
   __shared__ double s_x[6][2 * XPOLY];  // forward exchange, then the transformed digits; then the packed integers
   __shared__ double s_h[6][2 * HCOMP];  // inverse exchanges
