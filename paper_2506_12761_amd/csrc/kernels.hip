@@ -27,28 +27,6 @@ __device__ __forceinline__ KsItem ks_item(const KsSource& src, uint32_t t) {
 // Key preparation
 // ---------------------------------------------------------------------------
 
-// Double-double arithmetic: an unevaluated sum h + l, l a few ulp of h.  The
-// sums are never normalised on the way (l stays small over nine stages), which
-// takes a third of the operations away; against 128-bit arithmetic the
-// transform's error, relative in the 2-norm, stays below 1e-15 of 2^-53 before
-// its one rounding and below 0.47 of it after.
-struct DD {
-  double h, l;
-};
-__device__ __forceinline__ DD dd_add(DD a, DD b) {
-#pragma clang fp contract(off)
-  const double s = a.h + b.h, bb = s - a.h;
-  return {s, ((a.h - (s - bb)) + (b.h - bb)) + (a.l + b.l)};
-}
-__device__ __forceinline__ DD dd_neg(DD a) { return {-a.h, -a.l}; }
-__device__ __forceinline__ DD dd_dot(DD w, DD v, DD x, DD y) {  // w v + x y
-#pragma clang fp contract(off)
-  const double p = w.h * v.h, e = __builtin_fma(w.h, v.h, -p), q = x.h * y.h, f = __builtin_fma(x.h, y.h, -q);
-  const double s = p + q, bb = s - p;
-  const double lo = __builtin_fma(w.h, v.l, __builtin_fma(w.l, v.h, __builtin_fma(x.h, y.l, x.l * y.h)));
-  return {s, ((p - (s - bb)) + (q - bb)) + ((e + f) + lo)};
-}
-
 // One workgroup of 256 threads per key polynomial and channel: splits the
 // words (fft.h), transforms in LDS (a butterfly per thread and stage), scales
 // by 1/512 and stores in layout 3, [8 registers][64 lanes].  Bound: double-
@@ -60,32 +38,21 @@ __global__ __launch_bounds__(256) void bk_transform_kernel(const uint32_t* __res
   __shared__ DD s_re[FFT_N], s_im[FFT_N];
   const uint32_t row = blockIdx.x / FFT_CHANNELS, ch = blockIdx.x % FFT_CHANNELS;  // row = i * 6 + r
   const uint32_t* a = bk_coeff + (size_t)row * 2 * RING_N;
-  auto word = [&](const uint32_t* p, uint32_t j, double* hi) -> double {  // lo; *hi
-    const int32_t k = (int32_t)p[j], lo = (int32_t)((uint32_t)k << (32 - KEY_SHIFT)) >> (32 - KEY_SHIFT);
-    *hi = (double)(((int64_t)k - lo) >> KEY_SHIFT);
-    return (double)lo;
-  };
-  auto value = [&](uint32_t j) -> double {
-    double ha, hb;
-    if (ch == 0) return word(a, j, &ha), ha;
-    if (ch == 1) return word(a + RING_N, j, &hb), hb;
-    return word(a, j, &ha) + (double)(1 << LO_SHIFT) * word(a + RING_N, j, &hb);
-  };
   for (uint32_t i = threadIdx.x; i < FFT_N; i += 256) {
-    s_re[i] = {value(i), 0.0};
-    s_im[i] = {value(i + FFT_N), 0.0};
+    s_re[i] = {key_value(ch, a, a + RING_N, i), 0.0};
+    s_im[i] = {key_value(ch, a, a + RING_N, i + FFT_N), 0.0};
   }
   const uint32_t t = threadIdx.x;
   for (int k = 0; k < 9; ++k) {
     __syncthreads();
     const uint32_t half = FFT_N >> (k + 1), b = t / half, u = b * 2 * half + t % half, v = u + half;
     const double4 w = dd_tw[(1 << k) + b];
-    const DD wr{w.x, w.y}, wi{w.z, w.w}, vr = s_re[v], vi = s_im[v], ur = s_re[u], ui = s_im[u];
-    const DD tr = dd_dot(wr, vr, dd_neg(wi), vi), ti = dd_dot(wr, vi, wi, vr);
-    s_re[u] = dd_add(ur, tr);
-    s_im[u] = dd_add(ui, ti);
-    s_re[v] = dd_add(ur, dd_neg(tr));
-    s_im[v] = dd_add(ui, dd_neg(ti));
+    DD vr = s_re[v], vi = s_im[v], ur = s_re[u], ui = s_im[u];
+    dd_bf(ur, ui, vr, vi, DD{w.x, w.y}, DD{w.z, w.w});
+    s_re[u] = ur;
+    s_im[u] = ui;
+    s_re[v] = vr;
+    s_im[v] = vi;
   }
   __syncthreads();
   // Rows in the order a step reads them: digit 0 of A, digit 0 of B, digit 1 of A, ...
