@@ -523,7 +523,7 @@ def main():
     ap.add_argument("--ks-gates-per-block", type=int, default=0, choices=(0, 128, 256, 512),
                     help="most gates a key-switching workgroup takes (0: library default)")
     ap.add_argument("--br-waves-per-rotation", type=int, default=-1, choices=(-1, 0, 1, 2, 4),
-                    help="wavefronts per blind rotation (0: automatic by launch size)")
+                    help="blind-rotation kernel: 1, 2 or 4 (vlp.h); 0: automatic by launch size")
     ap.add_argument("--serve", action="store_true", help="run the serving experiment instead")
     ap.add_argument("--table3", action="store_true", help="replay the paper's dataset shapes instead")
     ap.add_argument("--server-enc", action="store_true", help="time ServerEnc of a 65,536-record database instead")

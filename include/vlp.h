@@ -260,7 +260,10 @@ vlp_status vlp_program_destroy(vlp_program *prog);
 
 /* ---- Tuning knobs of the batched kernels (picked by the autotuner).
  * br_waves_per_rotation : the blind-rotation kernel:
- *                          1 = one wavefront per rotation;
+ *                          1 = one wavefront per rotation (with up to 4
+ *                              rotations per workgroup each takes a SIMD by
+ *                              itself: a CU runs four rotations at a time,
+ *                              further workgroups of a launch follow);
  *                          4 = six wavefronts per rotation (half the
  *                              latency or less, one rotation per workgroup
  *                              and CU at a time);
@@ -279,9 +282,10 @@ vlp_status vlp_program_destroy(vlp_program *prog);
  *                          br_rotations_per_block rotations per CU (not in
  *                          automatic mode)
  * ks_gates_per_block    : most gates a key-switching workgroup takes, sharing
- *                          its reads of the key (128, 256, 512 (default));
- *                          each launch picks the tile (up to this) and the
- *                          split of the coefficients over workgroups */
+ *                          its reads of the key (128, 256 or 512; 512, the
+ *                          default, is taken as 256, the largest tile); each
+ *                          launch picks the tile (up to this) and the split
+ *                          of the coefficients over workgroups */
 typedef struct {
     uint32_t br_rotations_per_block;
     uint32_t br_blocks_per_cu;

@@ -1,11 +1,11 @@
 """Autotuner for the batched kernels' launch shape, with a JSON cache.
 
 Two sweeps:
-  * launch shape -- wavefronts per blind rotation (1, 2, 4 or automatic),
-    rotations per workgroup, workgroups per CU a launch is sized for, gates
-    per key-switching workgroup -- timed
-    on a caller-supplied program (one full pass each), the fastest is set on
-    the context and cached per device and workload;
+  * launch shape -- the blind-rotation kernel (br_waves_per_rotation: 1, 2, 4
+    or automatic), rotations per workgroup, workgroups per CU a launch is sized
+    for, gates per key-switching workgroup -- timed on a caller-supplied program
+    (one full pass each), the fastest is set on the context and cached per
+    device and workload;
   * batch size -- blind rotations per launch from 256 to 16,384, timed with
     the elementwise bootstrap call, giving the throughput curve that tells how
     many independent gates a launch needs to fill the device.
@@ -20,10 +20,13 @@ from . import vlp
 
 CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuning_cache.json")
 
-# (wavefronts per rotation, rotations per workgroup, workgroups per CU, gates
-# per key-switching workgroup); 0 wavefronts per rotation = automatic by launch size
-SHAPES = ([(1, w, b, 512) for w in (1, 2, 4, 8) for b in (1, 2, 4) if w * b <= 8]
-          + [(r, q, b, k) for r in (0, 2) for (q, b) in ((1, 4), (2, 2), (4, 1)) for k in (128, 256, 512)]
+# (br_waves_per_rotation, rotations per workgroup, workgroups per CU, gates per
+# key-switching workgroup).  Shapes that launch the same are listed once: the
+# automatic choice (0) sets its own rotation knobs, 2 puts at most two rotations
+# in a workgroup, and key switching takes 512 gates per workgroup as 256.
+SHAPES = ([(0, 4, 1, k) for k in (128, 512)]
+          + [(1, w, b, 512) for w in (1, 2, 4, 8) for b in (1, 2, 4) if w * b <= 8]
+          + [(2, q, b, k) for (q, b) in ((1, 4), (2, 2)) for k in (128, 512)]
           + [(4, 1, b, 512) for b in (1, 2)])
 
 

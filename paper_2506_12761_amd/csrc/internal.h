@@ -104,8 +104,8 @@ int launch_server_enc(const uint32_t* pk, uint32_t* out, size_t count, const int
                       uint32_t l, void* stream);
 // Key switching of count items on the matrix cores, in launches of at most
 // KS_CHUNK gates; dig: device scratch of ks_digit_bytes(count) bytes;
-// gates_per_block is the most gates a workgroup takes (128, 256 or 512), cus
-// the device's CUs.
+// gates_per_block is the most gates a workgroup takes (128, 256 or 512, the
+// last taken as 256, the largest tile), cus the device's CUs.
 constexpr uint32_t KS_CHUNK = 16384;
 constexpr size_t ks_digit_bytes(size_t count) { return (count < KS_CHUNK ? count : KS_CHUNK) * (RING_N * 2); }
 int launch_ks_group(const KsSource& src, uint32_t count, const uint32_t* ksk, uint32_t* dig,
