@@ -705,6 +705,14 @@ def main():
         roofline.update({"traffic": traffic, "traffic_unit": "B per launch", "algorithmic_bytes_per_launch": alg_bytes,
                          "kernel": {0: "br1_kernel (br3_kernel, br6_kernel for short rounds)", 1: "br1_kernel",
                                     2: "br3_kernel", 4: "br6_kernel"}[launch["br_waves_per_rotation"]]})
+        # Beside the derived peak: the measured rate of the transforms' own butterflies
+        # (register-resident, every CU busy, the 6:3 forward:inverse mix of a CMux), each
+        # counted as the 6 FMAs that FMA_PER_BR counts.
+        mp = vlp.vlp_measure_fft_peak(0)
+        roofline["peak_measured"] = 6 * mp["mixed"] / 1e12
+        roofline["frac_of_peak_measured"] = roofline["achieved"] / roofline["peak_measured"]
+        log("measured complex-butterfly peak: %.3f T/s forward, %.3f T/s inverse, %.3f T/s mixed"
+            % (mp["fwd"] / 1e12, mp["inv"] / 1e12, mp["mixed"] / 1e12))
 
     config4 = None
     if not args.no_config4 and args.workload != "idm-65536":

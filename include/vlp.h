@@ -324,6 +324,12 @@ vlp_status vlp_profile_read(vlp_ctx *ctx, vlp_kernel_stats *br, vlp_kernel_stats
  * context to hold it). */
 vlp_status vlp_measure_modmul_peak(int device, double *fwd_per_s, double *inv_per_s, double *mixed_per_s);
 
+/* Measured double-precision peak: the same call for the butterflies that the
+ * library's transforms run (complex, on 512 points; a forward one is 6 FMAs, an
+ * inverse one 8 operations), *mixed_per_s for the 6:3 forward:inverse mix of a
+ * CMux.  Complex butterflies per second; otherwise as above. */
+vlp_status vlp_measure_fft_peak(int device, double *fwd_per_s, double *inv_per_s, double *mixed_per_s);
+
 /* Wait until all work enqueued on the context's stream has finished. */
 vlp_status vlp_sync(vlp_ctx *ctx);
 

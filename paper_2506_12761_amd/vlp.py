@@ -34,7 +34,7 @@ EXPORTS = [
     "vlp_program_create", "vlp_program_create_ex", "vlp_program_reset", "vlp_step", "vlp_program_run",
     "vlp_program_counts", "vlp_plan_counts", "vlp_plan_counts_ex", "vlp_plan_bytes", "vlp_plan_bytes_ex",
     "vlp_program_level_counts", "vlp_program_destroy", "vlp_get_tuning", "vlp_set_tuning", "vlp_sync",
-    "vlp_profile_enable", "vlp_profile_read", "vlp_measure_modmul_peak",
+    "vlp_profile_enable", "vlp_profile_read", "vlp_measure_modmul_peak", "vlp_measure_fft_peak",
 ]
 
 
@@ -120,6 +120,8 @@ def lib():
             "vlp_profile_read": (ctypes.c_int, [vp, P(vlp_kernel_stats), P(vlp_kernel_stats)]),
             "vlp_measure_modmul_peak": (ctypes.c_int, [ctypes.c_int, P(ctypes.c_double), P(ctypes.c_double),
                                                        P(ctypes.c_double)]),
+            "vlp_measure_fft_peak": (ctypes.c_int, [ctypes.c_int, P(ctypes.c_double), P(ctypes.c_double),
+                                                    P(ctypes.c_double)]),
         }
         for name, (res, args) in sig.items():
             f = getattr(L, name)
@@ -364,13 +366,22 @@ def vlp_profile_read(ctx) -> dict:
             "ks": {"launches": ks.launches, "items": ks.items, "ms": ks.ms}}
 
 
-def vlp_measure_modmul_peak(device: int = 0) -> dict:
-    """Measured butterfly rates of `device` (modular multiplications per second)."""
+def _measure(name: str, device: int) -> dict:
     f, i, m = ctypes.c_double(), ctypes.c_double(), ctypes.c_double()
-    st = lib().vlp_measure_modmul_peak(device, ctypes.byref(f), ctypes.byref(i), ctypes.byref(m))
+    st = getattr(lib(), name)(device, ctypes.byref(f), ctypes.byref(i), ctypes.byref(m))
     if st != VLP_OK:
-        raise VlpError(st, "vlp_measure_modmul_peak failed")
+        raise VlpError(st, name + " failed")
     return {"fwd": f.value, "inv": i.value, "mixed": m.value}
+
+
+def vlp_measure_modmul_peak(device: int = 0) -> dict:
+    """Measured rates of `device` (residue butterflies per second)."""
+    return _measure("vlp_measure_modmul_peak", device)
+
+
+def vlp_measure_fft_peak(device: int = 0) -> dict:
+    """Measured rates of `device` (complex double-precision butterflies per second)."""
+    return _measure("vlp_measure_fft_peak", device)
 
 
 # ---------------------------------------------------------------------------
