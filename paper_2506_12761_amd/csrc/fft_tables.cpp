@@ -20,7 +20,22 @@ void stage_twiddle(int k, int b, long double* c, long double* s) {
 }  // namespace
 
 void make_fft_tables(FftTables* t) {
-  long double c, s;
+  // Every stage's twiddles once (511 sines and cosines); the lanes' are copies.
+  for (int e = 0; e < 4; ++e) t->dd[0][e] = 0;
+  for (int k = 0; k < 9; ++k)
+    for (int b = 0; b < (1 << k); ++b) {
+      long double c, s;
+      stage_twiddle(k, b, &c, &s);
+      double* d = t->dd[(1 << k) + b];
+      d[0] = (double)c;
+      d[1] = (double)(c - (long double)d[0]);
+      d[2] = (double)s;
+      d[3] = (double)(s - (long double)d[2]);
+    }
+  auto put = [t](double (&to)[2], int k, int b) {
+    to[0] = t->dd[(1 << k) + b][0];
+    to[1] = t->dd[(1 << k) + b][2];
+  };
   for (int L = 0; L < 64; ++L) {
     const int rho = L & 15, i4 = L >> 5, i3 = (L >> 4) & 1;
     const int i8 = L >> 5;  // of layout 4
@@ -28,11 +43,7 @@ void make_fft_tables(FftTables* t) {
     const int tail = (rho << 3) | (i4 << 2) | (i3 << 1);  // block of stage 7 with i2 = 0
     const int b_of[11] = {rho,          rho << 1, rho << 2,       (rho << 2) | 2, tail, tail << 1, (tail << 1) | 2,
                           i8 << 2, (i8 << 2) | 2, i8 << 1, i8};
-    for (int e = 0; e < 11; ++e) {
-      stage_twiddle(k_of[e], b_of[e], &c, &s);
-      t->lane[e][L][0] = (double)c;
-      t->lane[e][L][1] = (double)s;
-    }
+    for (int e = 0; e < 11; ++e) put(t->lane[e][L], k_of[e], b_of[e]);
   }
   // Half-size inverse (i8 = hf): stages 8, 7 in lane (i3 i2 | i4 | i7 i6 i5),
   // 6, 5 in lane (i1 i0 | i4 | i7 i6 i5), 4, 3 in lane (i7 i6 | i3..i0), 2, 1 uniform.
@@ -43,22 +54,17 @@ void make_fft_tables(FftTables* t) {
       const int mid = (hf << 2) | (L >> 4);                                                    // i8 i7 i6
       const int k_of[8] = {8, 7, 6, 5, 4, 3, 2, 1};
       const int b_of[8] = {b7 << 1, b7, ((top << 1) | i4) << 1, (top << 1) | i4, mid << 1, mid, hf << 1, hf};
-      for (int e = 0; e < 8; ++e) {
-        stage_twiddle(k_of[e], b_of[e], &c, &s);
-        t->half[hf][e][L][0] = (double)c;
-        t->half[hf][e][L][1] = (double)s;
-      }
+      for (int e = 0; e < 8; ++e) put(t->half[hf][e][L], k_of[e], b_of[e]);
     }
-  for (int k = 0; k < 9; ++k)
-    for (int b = 0; b < (1 << k); ++b) {
-      stage_twiddle(k, b, &c, &s);
-      double* d = t->dd[(1 << k) + b];
-      d[0] = (double)c;
-      d[1] = (double)(c - (long double)d[0]);
-      d[2] = (double)s;
-      d[3] = (double)(s - (long double)d[2]);
-    }
-  for (int e = 0; e < 4; ++e) t->dd[0][e] = 0;
+}
+
+const FftTables& fft_tables() {
+  static const FftTables tables = [] {
+    FftTables t;
+    make_fft_tables(&t);
+    return t;
+  }();
+  return tables;
 }
 
 }  // namespace vlp

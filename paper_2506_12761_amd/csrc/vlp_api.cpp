@@ -344,11 +344,9 @@ extern "C" vlp_status vlp_ctx_create(vlp_ctx** out, const vlp_params* p, int dev
     delete ctx;
     return VLP_EHIP;
   }
-  std::vector<FftTables> host(1);
-  make_fft_tables(host.data());
   vlp_status st = dev_alloc(ctx, (void**)&ctx->tables, sizeof(FftTables));
   if (st == VLP_OK) {
-    e = hipMemcpy(ctx->tables, host.data(), sizeof(FftTables), hipMemcpyHostToDevice);
+    e = hipMemcpy(ctx->tables, &fft_tables(), sizeof(FftTables), hipMemcpyHostToDevice);
     if (e != hipSuccess) st = fail(ctx, VLP_EHIP, "table upload: %s", hipGetErrorString(e));
   }
   if (st != VLP_OK) {
