@@ -149,10 +149,10 @@ __device__ __forceinline__ void bf_inv(Cplx& x, Cplx& y, double sr, double si) {
 
 // Layout 1: position i = 32 q + l, register q = 0..15, l = lane & 31; the two
 // half-wavefronts hold two polynomials.  Stages 0-3 (register bits 3-0).
-template <int K, int PAIRS = 8>
+template <int K>
 __device__ __forceinline__ void fwd_stage1(Cplx (&z)[16]) {
 #pragma unroll
-  for (int p = 0; p < PAIRS; ++p) {
+  for (int p = 0; p < 8; ++p) {
     constexpr int B = 8 >> K;  // register stride
     const int q = ((p / B) * 2 * B) + (p % B);
     const int b = q >> (4 - K);

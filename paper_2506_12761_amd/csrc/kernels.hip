@@ -149,9 +149,6 @@ __device__ __forceinline__ uint32_t abar_of(const BrItem& I, uint32_t w) {
   return (x + (1u << 20)) >> 21;
 }
 
-
-// Products of one transformed digit polynomial of each accumulator half with
-// its three key channels, added to (FIRST: starting) the sums.
 // The key is one stream of batches of 8 values per lane (one transformed
 // digit polynomial's products with one channel), read in order; v holds the
 // batch that comes next.  Each value is replaced by the one of the batch after
@@ -166,9 +163,9 @@ __device__ __forceinline__ void key_load(double2 (&v)[8], __amdgpu_buffer_rsrc_t
 // the wavefronts find them in L2: each XCD has its own L2, and its workgroups
 // (blockIdx mod 8) share the step's 18 batches among their wavefronts (`batch`
 // counts an XCD's wavefronts, those past 18 touch nothing), one 128-byte line
-// per lane.  1,024 rotations with the key in HBM: 9.2 -> 7.7 ms (in the
-// last-level cache 7.6 ms either way); 2,048: 13.5 -> 12.9 ms.  The other
-// kernels hold the loads of a whole step or of its longest wait and gain
+// per lane.  1,024 rotations with the key in HBM: 8.00 -> 7.07 ms (in the
+// last-level cache 7.00 -> 7.06); 2,048: 12.35 -> 11.96 ms (11.96 either way).
+// The other kernels hold the loads of a whole step or of its longest wait and gain
 // nothing (br6_kernel, 256: 3.05 -> 2.93 ms, but 2.77 -> 2.93 from the cache).
 constexpr int PREFETCH_STEPS = 4, NUM_XCD = 8, STEP_BATCHES = 2 * ELL * FFT_CHANNELS;
 __device__ __forceinline__ uint32_t key_touch(__amdgpu_buffer_rsrc_t key, int lane, int i, int batch) {
@@ -216,7 +213,8 @@ __device__ __forceinline__ void key_warm(const BrItem* __restrict__ items, uint3
   }
 }
 
-// s += a * v for one channel (FIRST: s = a * v); NEXT: replaces v by the batch at offset off.
+// Products of one transformed digit polynomial with one of its key channels:
+// s += a * v (FIRST: s = a * v); NEXT: replaces v by the batch at offset off.
 template <bool FIRST, bool NEXT>
 __device__ __forceinline__ void key_products(Cplx (&s)[8], const Cplx (&a)[8], double2 (&v)[8],
                                              __amdgpu_buffer_rsrc_t key, int lane16, int off) {
@@ -521,7 +519,7 @@ __global__ __launch_bounds__(192 * BR3_ROT) __attribute__((amdgpu_waves_per_eu(2
   const BrItem I = items[active ? idx : count - 1];  // an idle rotation repeats the last one and writes nothing
   const int j1 = j == 2 ? 0 : j + 1, j2 = j == 0 ? 2 : j - 1;  // (j + 1) mod 3, (j + 2) mod 3
   double(*X)[REGION] = s_x[rot_i];
-  // Regions: wavefront j's first (and, ROOMY, second) outgoing partial sums;
+  // Regions: wavefront j's first and second outgoing partial sums;
   // the region that only this wavefront reads last is its inverse exchange.
   double* mine = X[j];
   double* mine2 = X[3 + j];

@@ -174,6 +174,7 @@ bool ranges_overlap(const void* a, size_t an, const void* b, size_t bn) {
   return pa < pb + bn && pb < pa + an;
 }
 
+KsSource ks_array(const KsItem* items) { return KsSource{items, {}}; }
 
 int mark_begin(vlp_ctx* ctx);
 void mark_end(vlp_ctx* ctx, int id, int kind, uint64_t items);
@@ -189,8 +190,6 @@ void mark_end(vlp_ctx* ctx, int id, int kind, uint64_t items);
 // except that 4 to 5 per CU run as 4 and 1 (9.9 ms, the sum of both) and 5 to 6
 // as 4 and 2 (11.5 ms); splitting the others gains nothing (2 as 1 and 1: 5.5 ms; 3 as 2
 // and 1: 7.2 ms; 7 as 4, 2 and 1: 14.3 ms).
-KsSource ks_array(const KsItem* items) { return KsSource{items, {}}; }
-
 struct BrRound {
   uint32_t waves, rot_per_block, rotations;
 };
