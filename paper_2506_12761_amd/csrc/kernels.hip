@@ -199,12 +199,12 @@ __device__ __forceinline__ void key_warm(const BrItem* __restrict__ items, uint3
                                          uint32_t parts) {
   const void *const first = items[0].bk, *const last = items[count - 1].bk;
   const uint32_t stride = parts * WARM_THREADS;
-  auto touch = [&](const void* bk, uint32_t e) {  // lines past the key's end are out of the buffer's range: nothing is read
+  auto touch = [&](const void* bk, uint32_t e) {  // line KEY_LINES is out of the buffer's range: nothing is read
     const __amdgpu_buffer_rsrc_t key = __builtin_amdgcn_make_buffer_rsrc((void*)bk, 0, (int)BK_FFT_BYTES, 0x00027000);
     uint32_t x[WARM_LOADS];
 #pragma unroll
     for (uint32_t u = 0; u < WARM_LOADS; ++u)
-      x[u] = __builtin_amdgcn_raw_buffer_load_b32(key, (int)((e + u * stride) * 128), 0, 0);
+      x[u] = __builtin_amdgcn_raw_buffer_load_b32(key, (int)(min(e + u * stride, KEY_LINES) * 128), 0, 0);
     asm volatile("" ::"v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]));
   };
   for (uint32_t e = part * WARM_THREADS + threadIdx.x; e < KEY_LINES; e += WARM_LOADS * stride) {
