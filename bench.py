@@ -58,7 +58,7 @@ PEAK_FMA = 256 * 64 * 2.4e9
 # workload, from two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE;
 # copy-calibrated), valid only for the kernel sources it was measured on
 # (their sha256 prefix) and the launch shape it was measured with.
-TRAFFIC_MEASURED = {"kernel_sha": "10f2c284bda479d5", "bytes_per_launch": 906100000,
+TRAFFIC_MEASURED = {"kernel_sha": "758d59e48ec69feb", "bytes_per_launch": 896300000,
                     "launch": {"br_waves_per_rotation": 0, "br_rotations_per_block": 4, "br_blocks_per_cu": 1,
                                "ks_gates_per_block": 512}}
 KERNEL_SOURCES = ("kernels.hip", "fft.h", "vlp_api.cpp")
